@@ -1,0 +1,37 @@
+"""Edges of the channel-norm pass on the GPU: tiles of 64 / 32 rows and 64 columns with remainders,
+rows that start on 16 bytes and rows that do not (two load paths of one kernel), runs of one row,
+runs cut by tiles and chunks, and several chunks; every case against a binary64 sum."""
+import numpy as np
+import pytest
+import torch
+
+import workloads
+from test_parity_gpu import DEV
+
+pytestmark = pytest.mark.gpu
+
+
+def reference(x, grows, groups, div, rep):
+    r = torch.arange(x.shape[0], device=x.device)
+    g = (r // grows) % groups // div
+    out = torch.zeros((groups // div, x.shape[1]), dtype=torch.float64, device=x.device)
+    out.index_add_(0, g, x.double().square())
+    return out.repeat_interleave(rep, 0).cpu().numpy()
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 8), (63, 64), (65, 72), (255, 200), (257, 63), (700, 136), (33, 1)])
+@pytest.mark.parametrize("args", [(1, 1, 1, 1), (5, 1, 1, 2), (1, 4, 1, 1), (1, 4, 2, 3), (31, 3, 1, 1), (300, 2, 2, 1)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_norms_edges(rows, cols, args, dtype):
+    import paper_2606_07618_amd as nv
+    g = workloads.generator(DEV, 91, rows, cols)
+    x = torch.randn((rows, cols), generator=g, device=DEV).to(dtype)
+    got = nv.channel_sq_norms(x, *args)
+    buf = torch.empty(x.numel() + 1, dtype=dtype, device=DEV)
+    buf[1:].copy_(x.reshape(-1))
+    shifted = nv.channel_sq_norms(buf[1:].view(rows, cols), *args)   # no row starts on 16 bytes
+    torch.cuda.synchronize()
+    ref = reference(x, *args)
+    # at most 700 additions of rounding 2^-53 each, then one rounding to binary32 (2^-24)
+    assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= ref * (2.0 ** -24 + 700 * 2.0 ** -53))
+    assert torch.equal(got.view(torch.int32), shifted.view(torch.int32))    # one order of additions

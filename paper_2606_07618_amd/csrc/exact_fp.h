@@ -49,14 +49,12 @@ __device__ __forceinline__ int round_fp4_index(double a, double s) {
     return k;
 }
 
-// Largest code c in 0..126 with E4M3(c) <= v (v >= 0; +inf gives 126).
+// Largest code c in 0..126 with E4M3(c) <= v (v >= 0; +inf gives 126), from v's bits: a normal
+// value's code is its exponent and top three fraction bits, below 2^-6 the codes are 2^-9 apart.
 __device__ __forceinline__ int floor_e4m3(double v) {
-    int lo = 0, hi = 126;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (e4m3_f64(mid) <= v) lo = mid; else hi = mid - 1;
-    }
-    return lo;
+    if (v >= 448.0) return 126;
+    if (v < 0x1p-6) return (int)(v * 512.0);
+    return (int)((uint64_t)__double_as_longlong(v) >> 49) - (1016 << 3);
 }
 
 }  // namespace nvfp4_exact

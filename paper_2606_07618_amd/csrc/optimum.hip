@@ -11,11 +11,11 @@
 // consecutive breakpoints the rounding of every element is fixed, so L = A - 2 B s + C s^2
 // there and its minimum on the closed piece is at B / C clamped to the piece.
 //
-// Work layout: one wavefront per micro-block.  The wave writes the block's 7 n breakpoints
-// to LDS (padded with +inf to a power of two), sorts them with a bitonic network, and then
-// every lane scores every 64th piece: the piece's rounding indices are taken at its
-// midpoint, its coefficients summed in element order, and its minimum formed as above.  A
-// wave-wide lexicographic minimum (loss, piece index) picks the optimum, the lowest piece on
+// Work layout: one wavefront per micro-block (two at n = 64, four at n = 128).  It sorts the
+// block's 7 n breakpoints (padded with +inf to 8 n) with a bitonic network, and then every lane
+// scores every 64th piece: the roundings on the piece follow from which breakpoints lie below
+// it, its coefficients are summed in element order, and its minimum formed as above.  A
+// lexicographic minimum (loss, piece index) picks the optimum, the lowest piece on
 // a tie, and the all-zero reconstruction (s -> infinity) ahead of any piece of equal loss.
 // Everything is binary64 with correctly rounded division and no contraction, so each
 // value is a fixed sequence of IEEE operations.  This is analysis work, bound by binary64
@@ -24,6 +24,8 @@
 
 #include <math.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "exact_fp.h"
 #include "nvfp4ss.h"
@@ -45,22 +47,6 @@ __device__ __forceinline__ float load_elem<uint16_t>(const uint16_t* x, int64_t 
     return __uint_as_float((uint32_t)x[i] << 16);        // bfloat16 -> binary32, exact
 }
 
-// Exact loss of one block at the scale s, summed in element order (binary64).
-template <int N>
-__device__ double block_loss_f64(const float* ys, const float* ws, bool weighted, double s) {
-    double J = 0.0;
-#pragma unroll 2
-    for (int i = 0; i < N; ++i) {
-        const double a = fabs((double)ys[i]);
-        const double g = e2m1_value(round_fp4_index(a, s));
-        const double e = a - g * s;
-        double t = e * e;
-        if (weighted) t = (double)ws[i] * t;
-        J = J + t;
-    }
-    return J;
-}
-
 struct Best {
     double val, s;
     int seg;                 // -1: the all-zero reconstruction
@@ -70,143 +56,376 @@ __device__ __forceinline__ bool better(const Best& a, const Best& b) {
     return a.val < b.val || (a.val == b.val && a.seg < b.seg);
 }
 
+// How a block of N elements is spread over a workgroup.  Its 7 N breakpoints, padded to 8 N, sit
+// kPer to a thread; one wave up to N = 32, more above, so that a CU holds at least five waves per
+// SIMD whatever the block's LDS (binary64 chains and LDS reads need them to overlap).
 template <int N>
-struct Pow2Breaks {
-    static constexpr int M = 7 * N;
-    static constexpr int P = M <= 128 ? 128 : M <= 256 ? 256 : M <= 512 ? 512 : 1024;
+struct Spread {
+    static constexpr int kWaves = N <= 32 ? 1 : N / 32;
+    static constexpr int kThreads = kWaves * kWave;
+    static constexpr int kBreaks = 8 * N;
+    static constexpr int kPer = kBreaks / kThreads;            // 2 at N = 16, else 4
+    // Blocks a workgroup takes together: their elements are loaded, and their FP8 neighbours
+    // scored, by full waves.
+    // (At N = 32 the extra registers cost the fifth wave per SIMD and 5 % of the time.)
+    static constexpr int kBatch = N == 16 ? 4 : 1;
 };
 
+// v of lane (lane ^ D), D < 16 (DPP: quad permutations, a half-row mirror, a row rotation).
+template <int D>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+    static_assert(D == 1 || D == 2 || D == 4 || D == 8, "inside a row of 16 lanes");
+    auto dpp = [](uint32_t t, auto ctrl) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)t, decltype(ctrl)::value, 0xF, 0xF, true);
+    };
+    if constexpr (D == 1) return dpp(v, std::integral_constant<int, 0xB1>());      // quad_perm 1 0 3 2
+    if constexpr (D == 2) return dpp(v, std::integral_constant<int, 0x4E>());      // quad_perm 2 3 0 1
+    if constexpr (D == 4)                                                          // 7 - l, then 3 - l
+        return dpp(dpp(v, std::integral_constant<int, 0x141>()), std::integral_constant<int, 0x1B>());
+    return dpp(v, std::integral_constant<int, 0x128>());                           // row_ror 8
+}
+
+template <int D>
+__device__ __forceinline__ double exchange_other(double v) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    return __longlong_as_double(
+        (long long)(((uint64_t)lane_xor<D>((uint32_t)(b >> 32)) << 32) | lane_xor<D>((uint32_t)b)));
+}
+
+// One compare-exchange between lanes D apart: the lane keeps the smaller of the two keys, or the
+// larger.  (Equal keys are only the +inf padding.)
+template <int D>
+__device__ __forceinline__ double exchange(double v, bool keep_min) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    double lo_lane = v, other;
+    if constexpr (D < 16) {
+        other = exchange_other<D>(v);
+    } else {                   // rows (16) or halves (32) of the two operands swap: both lanes of a
+                               // pair see the lower lane's key, then the upper lane's
+        const auto h = D == 16 ? __builtin_amdgcn_permlane16_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false)
+                               : __builtin_amdgcn_permlane32_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+        const auto l = D == 16 ? __builtin_amdgcn_permlane16_swap((uint32_t)b, (uint32_t)b, false, false)
+                               : __builtin_amdgcn_permlane32_swap((uint32_t)b, (uint32_t)b, false, false);
+        lo_lane = __longlong_as_double((long long)(((uint64_t)h[0] << 32) | l[0]));
+        other = __longlong_as_double((long long)(((uint64_t)h[1] << 32) | l[1]));
+    }
+    return (lo_lane < other) == keep_min ? lo_lane : other;
+}
+
+// Ascending bitonic sort of the kBreaks keys, thread t holding positions kPer t + r; the runs of
+// eight (one element's breakpoints) come in sorted, alternately up and down.  Strides inside a
+// thread and inside a wave stay in registers; the few across waves go through LDS.
+template <int N>
+__device__ __forceinline__ void sort_keys(double (&k)[Spread<N>::kPer], double* lds) {
+    using Sp = Spread<N>;
+    constexpr int R = Sp::kPer;
+    const int tid = threadIdx.x;
+    auto stage = [&](auto size_c, auto stride_c) {
+        constexpr int size = decltype(size_c)::value, stride = decltype(stride_c)::value;
+        const bool asc = size >= Sp::kBreaks || (tid & (size / R)) == 0;
+        if constexpr (stride < R) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (r & stride) continue;
+                const double u = k[r], v = k[r + stride];
+                const bool keep = (u < v) == asc;
+                k[r] = keep ? u : v;
+                k[r + stride] = keep ? v : u;
+            }
+        } else {
+            constexpr int d = stride / R;                      // threads apart
+            const bool keep_min = ((tid & d) == 0) == asc;
+            if constexpr (d < kWave) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) k[r] = exchange<d>(k[r], keep_min);
+            } else {
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < R; ++r) lds[r * Sp::kThreads + tid] = k[r];
+                __syncthreads();
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const double o = lds[r * Sp::kThreads + (tid ^ d)];
+                    k[r] = (k[r] < o) == keep_min ? k[r] : o;
+                }
+            }
+        }
+    };
+    auto merge = [&](auto size_c) {
+        constexpr int size = decltype(size_c)::value;
+        if constexpr (size <= Sp::kBreaks) {
+            auto down = [&](auto self, auto stride_c) {
+                constexpr int stride = decltype(stride_c)::value;
+                stage(size_c, stride_c);
+                if constexpr (stride > 1) self(self, std::integral_constant<int, stride / 2>());
+            };
+            down(down, std::integral_constant<int, size / 2>());
+        }
+    };
+    merge(std::integral_constant<int, 16>());
+    merge(std::integral_constant<int, 32>());
+    merge(std::integral_constant<int, 64>());
+    merge(std::integral_constant<int, 128>());
+    merge(std::integral_constant<int, 256>());
+    merge(std::integral_constant<int, 512>());
+    merge(std::integral_constant<int, 1024>());
+}
+
+// 420 / (4 m_j) for the midpoints 4 m_j = 1, 3, 5, 7, 10, 14, 20: nine bits each.
+__device__ __forceinline__ double break_factor(int j) {
+    constexpr uint64_t packed = 420ull | 140ull << 9 | 84ull << 18 | 60ull << 27 | 42ull << 36 |
+                                30ull << 45 | 21ull << 54;
+    return (double)(int)((packed >> (9 * j)) & 511u);
+}
+
+// RN(k / 105) for a key k (24 + 9 bits): a multiply by the rounded reciprocal and one exact
+// remainder's correction (Markstein).  NaN for the padding, whose quotient nothing reads.
+__device__ __forceinline__ double div_105(double k) {
+    constexpr double r = 1.0 / 105.0;
+    const double q = k * r;
+    return fma(fma(-q, 105.0, k), r, q);
+}
+
+// The least value of a wave, in every lane.
+__device__ __forceinline__ double wave_min(double v) {
+    v = fmin(v, exchange_other<1>(v));
+    v = fmin(v, exchange_other<2>(v));
+    v = fmin(v, exchange_other<4>(v));
+    v = fmin(v, exchange_other<8>(v));
+    v = fmin(v, exchange<16>(v, true));
+    return fmin(v, exchange<32>(v, true));
+}
+
+__device__ __forceinline__ int wave_min(int v) {
+    v = min(v, (int)lane_xor<1>((uint32_t)v));
+    v = min(v, (int)lane_xor<2>((uint32_t)v));
+    v = min(v, (int)lane_xor<4>((uint32_t)v));
+    v = min(v, (int)lane_xor<8>((uint32_t)v));
+    const auto h = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    v = min((int)h[0], (int)h[1]);
+    const auto q = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    return min((int)q[0], (int)q[1]);
+}
+
+__device__ __forceinline__ double read_lane(double v, int lane) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double(
+        (long long)(((uint64_t)hi << 32) | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane)));
+}
+
+// The breakpoints |y| / m are sorted by the key |y| (420 / 4m), which is exact in binary64 (24 + 9
+// bits) and orders and ties them as the quotients do: two different quotients of 24-bit values by
+// these midpoints are at least 2^-29 apart, so their roundings neither meet nor cross, and a
+// piece's midpoint is never within rounding of a breakpoint.  The key's low bits are free and
+// carry the element.  So on the piece above the first `seg` breakpoints, an element has passed 7
+// minus as many midpoints as it has breakpoints among those: a count of its positions below seg
+// (a compare, and a bit count below the lane), instead of comparisons with seven products per
+// element and piece, and the terms it adds to B and C come from a table of its eight roundings,
+// formed once.  VALU issue bounds the kernel (781 instructions a block at N = 16, of
+// which the sort and the pieces take 300 each): [4096, 4096] bfloat16 with weights 1.20 ms (a
+// comparison with each product, breakpoints sorted in LDS, the FP8 losses on one lane: 4.19 ms);
+// at N = 32, 64, 128 0.83, 0.71 and 0.61 ms for half, a quarter and an eighth of the rows (2.92,
+// 2.23, 2.46).  Five waves per SIMD: four cost 6 % at N = 64 and 128.
 template <typename In, int N>
-__global__ __launch_bounds__(kWave) void optimum_kernel(const In* __restrict__ x,
-                                                        const float* __restrict__ colw,
-                                                        const float* __restrict__ tensor_scale,
-                                                        int64_t nblocks, int64_t bpr,
-                                                        double* __restrict__ opt_loss,
-                                                        double* __restrict__ opt_scale,
-                                                        uint8_t* __restrict__ fp8_code,
-                                                        double* __restrict__ fp8_loss) {
-    constexpr int P = Pow2Breaks<N>::P;
-    __shared__ double bp[P];
-    __shared__ float ys[N], wsh[N];
-    __shared__ double ad[N], wd[N], wad[N];   // |y|, w, w |y| in binary64 (per block)
-    __shared__ double g_tab[8];
-    if (threadIdx.x < 8) g_tab[threadIdx.x] = e2m1_value(threadIdx.x);
-    const int lane = threadIdx.x;
+__global__ __launch_bounds__(Spread<N>::kThreads, 5) void optimum_kernel(const In* __restrict__ x,
+                                                                     const float* __restrict__ colw,
+                                                                     const float* __restrict__ tensor_scale,
+                                                                     int64_t nblocks, int64_t bpr,
+                                                                     double* __restrict__ opt_loss,
+                                                                     double* __restrict__ opt_scale,
+                                                                     uint8_t* __restrict__ fp8_code,
+                                                                     double* __restrict__ fp8_loss) {
+    using Sp = Spread<N>;
+    constexpr int R = Sp::kPer, W = Sp::kWaves, P = Sp::kBreaks;
+    constexpr int KB = Sp::kBatch;
+    __shared__ alignas(16) double key[P];     // sorted keys, then breakpoints, then FP8 loss terms
+    __shared__ alignas(16) double2 tab[P];    // tab[8 i + c]: element i's terms of B and C with c
+                                              // of its breakpoints passed
+    __shared__ alignas(16) double ads[KB][N], wds[KB][N], aas[KB][N];   // |y|, w, w y^2
+    __shared__ uint32_t first[W > 1 ? W : 1][W > 1 ? N : 1];   // breakpoints below a wave's pieces
+    __shared__ Best wave_best[W];
+    __shared__ double scale_of[KB];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const float S = tensor_scale[0];
     const bool weighted = colw != nullptr;
 
-    for (int64_t blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
-        const int64_t kb = blk % bpr;
-        int nonzero = 0;
-        for (int i = lane; i < N; i += kWave) {
-            const float y = __fdiv_rn(load_elem<In>(x, blk * N + i), S);   // y = RN32(x / S)
-            ys[i] = y;
-            wsh[i] = weighted ? colw[kb * N + i] : 1.0f;
-            const double a = fabs((double)y);
-            const double wi = weighted ? (double)wsh[i] : 1.0;
-            ad[i] = a;
-            wd[i] = wi;
-            wad[i] = wi * a;
-        }
-        __syncthreads();
-        for (int i = 0; i < N; i += kWave) {
-            const bool nz = i + lane < N && ys[i + lane] != 0.0f;
-            nonzero += __popcll(__ballot(nz));
-        }
-        const int nb = 7 * nonzero;
-        for (int t = lane; t < P; t += kWave) {
-            double v = INFINITY;
-            if (t < 7 * N) {
-                const double a = fabs((double)ys[t / 7]);
-                if (a != 0.0) v = a / e2m1_mid(t % 7);
+    const int64_t kb_step = (int64_t)gridDim.x * KB % bpr;
+    int64_t kb = ((int64_t)blockIdx.x * KB + tid / N) % bpr;   // column of this thread's block
+    for (int64_t blk0 = (int64_t)blockIdx.x * KB; blk0 < nblocks; blk0 += (int64_t)gridDim.x * KB) {
+        if (tid < N * KB) {
+            double a = 0.0, wi = 1.0;
+            if (blk0 + tid / N < nblocks) {
+                const float y = __fdiv_rn(load_elem<In>(x, blk0 * N + tid), S);   // y = RN32(x / S)
+                a = fabs((double)y);
+                if (weighted) wi = (double)colw[kb * N + tid % N];
             }
-            bp[t] = v;
+            ads[0][tid] = a;
+            wds[0][tid] = wi;
+            aas[0][tid] = wi * a * a;
         }
         __syncthreads();
-        // ascending bitonic sort of the P breakpoints (+inf padding sorts last)
-        for (int size = 2; size <= P; size <<= 1) {
-            for (int ls = __builtin_ctz(size) - 1; ls >= 0; --ls) {   // stride = 2^ls
-                const int stride = 1 << ls;
-                for (int t = lane; t < P / 2; t += kWave) {
-                    const int i = ((t >> ls) << (ls + 1)) + (t & (stride - 1));
-                    const int j = i + stride;
-                    const bool asc = (i & size) == 0;
-                    const double u = bp[i], v = bp[j];
-                    if ((u > v) == asc) {
-                        bp[i] = v;
-                        bp[j] = u;
-                    }
+        for (int b = 0; b < KB && blk0 + b < nblocks; ++b) {
+            const double *ad = ads[b], *wd = wds[b], *aa = aas[b];
+            int nb = 0;                            // breakpoints: 7 for each non-zero element
+#pragma unroll
+            for (int i = 0; i < N; i += kWave) nb += 7 * __popcll(__ballot(i + lane < N && ad[(i + lane) & (N - 1)] != 0.0));
+            double k[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int p = tid * R + r, e = p >> 3, h = p & 7;
+                // even elements rise (m from the largest), odd ones fall; the padding is +inf
+                const bool up = (e & 1) == 0, pad = h == (up ? 7 : 0);
+                const double a = ad[e];
+                const double v = a * break_factor(pad ? 0 : up ? 6 - h : h - 1);
+                k[r] = pad || a == 0.0 ? INFINITY
+                                       : __longlong_as_double(__double_as_longlong(v) | (long long)e);
+                // the element's terms with h breakpoints passed: rounded to value 7 - h
+                const double g = e2m1_value(7 - h), w = wd[e];
+                tab[p] = a == 0.0 ? make_double2(0.0, 0.0) : make_double2(w * a * g, w * g * g);
+            }
+            sort_keys<N>(k, key);
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < R; ++r) key[tid * R + r] = k[r];
+            __syncthreads();
+            // wave v's pieces are seg = 64 (R v + t) + lane; the breakpoint above each, its element
+            const int seg0 = kWave * R * wave;
+            uint32_t id[R];
+            double hi_bp[R];
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+                const uint64_t b = (uint64_t)__double_as_longlong(key[seg0 + kWave * t + lane]);
+                id[t] = seg0 + kWave * t + lane < nb ? (uint32_t)b & 127u : 128u;      // padding: none
+                hi_bp[t] = div_105(__longlong_as_double((long long)(b & ~127ull)));    // RN(|y| / m)
+            }
+            if constexpr (W > 1) {
+                const double from = key[seg0];
+                for (int i = lane; i < N; i += kWave) {
+                    uint32_t c = 0;
+#pragma unroll
+                    for (int j = 0; j < 7; ++j)
+                        c += __longlong_as_double(__double_as_longlong(ad[i] * break_factor(j)) | (long long)i) < from ? 1u : 0u;
+                    first[wave][i] = ad[i] != 0.0 ? c : 0u;
                 }
-                __syncthreads();
             }
-        }
+            __syncthreads();                       // the keys are used
+#pragma unroll
+            for (int t = 0; t < R; ++t) key[seg0 + kWave * t + lane] = hi_bp[t];
+            __syncthreads();
 
-        double A0 = 0.0;                       // the all-zero reconstruction: sum w y^2
-        for (int i = 0; i < N; ++i) {
-            const double a = (double)ys[i];
-            A0 += (weighted ? (double)wsh[i] : 1.0) * a * a;
-        }
-        Best best{A0, INFINITY, -1};
-        for (int seg = lane; seg <= nb; seg += kWave) {
-            const double lo = seg == 0 ? 0.0 : bp[seg - 1];
-            const double hi = seg == nb ? INFINITY : bp[seg];
-            if (!(hi > lo)) continue;
-            const double s_ref = seg == 0 ? 0.5 * hi : seg == nb ? 2.0 * lo : 0.5 * (lo + hi);
-            // A = sum w y^2 is the same on every piece (and equals A0 bit for bit: w |y| |y|
-            // and w y y round alike), so only B and C are summed here
-            const double A = A0;
-            double B = 0.0, C = 0.0;
+            double A = 0.0;                        // sum w y^2: the loss of the all-zero reconstruction
+            double B[R], C[R];
+#pragma unroll
+            for (int t = 0; t < R; ++t) B[t] = C[t] = 0.0;
 #pragma unroll 4
             for (int i = 0; i < N; ++i) {
-                const double g = g_tab[round_fp4_index(ad[i], s_ref)];
-                B += wad[i] * g;                 // (w |y|) g, as w * a * g associates
-                C += wd[i] * g * g;
+                uint32_t below = W > 1 ? first[wave][i] : 0u;
+                A += aa[i];
+#pragma unroll
+                for (int t = 0; t < R; ++t) {
+                    const uint64_t m = __ballot(id[t] == (uint32_t)i);
+                    const uint32_t c = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)m, below));
+                    const double2 v = tab[8 * i + c];              // c <= 7: an element has 7
+                    B[t] += v.x;
+                    C[t] += v.y;
+                    if (t + 1 < R) below += (uint32_t)__popcll(m);
+                }
             }
-            Best cand{0.0, 0.0, seg};
-            if (C <= 0.0) {
-                cand.val = A;
-                cand.s = s_ref;
-            } else {
-                double s = B / C;
-                if (s < lo) s = lo;
-                if (s > hi) s = hi;
-                if (s <= 0.0) continue;
-                double val = A - 2.0 * B * s + C * s * s;
-                if (val < 0.0) val = 0.0;
-                cand.val = val;
-                cand.s = s;
+            Best best{A, INFINITY, -1};
+#pragma unroll
+            for (int t = 0; t < R; ++t) {
+                const int seg = seg0 + kWave * t + lane;
+                const double lo = seg == 0 ? 0.0 : key[seg == 0 ? 0 : seg - 1];
+                const double hi = seg == nb ? INFINITY : hi_bp[t];
+                if (seg > nb || !(hi > lo)) continue;
+                const double s_ref = seg == 0 ? 0.5 * hi : seg == nb ? 2.0 * lo : 0.5 * (lo + hi);
+                Best cand{0.0, 0.0, seg};
+                if (C[t] <= 0.0) {
+                    cand.val = A;
+                    cand.s = s_ref;
+                } else {
+                    double s = B[t] / C[t];
+                    if (s < lo) s = lo;
+                    if (s > hi) s = hi;
+                    if (s <= 0.0) continue;
+                    double val = A - 2.0 * B[t] * s + C[t] * s * s;
+                    if (val < 0.0) val = 0.0;
+                    cand.val = val;
+                    cand.s = s;
+                }
+                if (better(cand, best)) best = cand;
             }
-            if (better(cand, best)) best = cand;
+            // the wave's least loss, the lowest piece on a tie (every lane holds at least the all-zero
+            // reconstruction)
+            {
+                const double least = wave_min(best.val);
+                const int seg = wave_min(best.val == least ? best.seg : INT32_MAX);
+                const uint64_t m = __ballot(best.val == least && best.seg == seg);
+                const int from = m ? (int)__builtin_ctzll(m) : 0;          // m = 0 only with NaN
+                best = Best{read_lane(best.val, from), read_lane(best.s, from), __builtin_amdgcn_readlane(best.seg, from)};
+            }
+            if constexpr (W > 1) {
+                if (lane == 0) wave_best[wave] = best;
+                __syncthreads();
+                best = wave_best[0];
+#pragma unroll
+                for (int v = 1; v < W; ++v)
+                    if (better(wave_best[v], best)) best = wave_best[v];
+            }
+            double J = best.val, s_opt = best.s;
+            if (nb == 0) {                          // all-zero block: zero loss at any scale
+                J = 0.0;
+                s_opt = 1.0;
+            }
+            if (tid == 0) {
+                opt_loss[blk0 + b] = J;
+                if (opt_scale) opt_scale[blk0 + b] = s_opt;
+                scale_of[b] = s_opt;
+            }
+            __syncthreads();                        // key and tab are reused
         }
-        for (int off = kWave / 2; off > 0; off >>= 1) {
-            Best o;
-            o.val = __shfl_xor(best.val, off, kWave);
-            o.s = __shfl_xor(best.s, off, kWave);
-            o.seg = __shfl_xor(best.seg, off, kWave);
-            if (better(o, best)) best = o;
-        }
-        double J = best.val, s_opt = best.s;
-        if (nb == 0) {                          // all-zero block: zero loss at any scale
-            J = 0.0;
-            s_opt = 1.0;
-        }
-        if (lane == 0) {
-            opt_loss[blk] = J;
-            if (opt_scale) opt_scale[blk] = s_opt;
-            if (fp8_code || fp8_loss) {
-                // the FP8 values just below and just above s_opt; the lower-loss one (the
-                // lower value on a tie); positive codes only
-                int cf = floor_e4m3(s_opt);
-                int cc = (e4m3_f64(cf) < s_opt && cf < 126) ? cf + 1 : cf;
+        if (fp8_code || fp8_loss) {
+            // the FP8 values just below and just above s_opt; the lower-loss one (the lower value
+            // on a tie); positive codes only.  One thread per term, then one lane per sum adds its
+            // N terms in element order.
+            auto neighbours = [&](double s, int& cf, int& cc) {
+                cf = floor_e4m3(s);
+                cc = (e4m3_f64(cf) < s && cf < 126) ? cf + 1 : cf;
                 cf = cf < 1 ? 1 : cf;
                 cc = cc < 1 ? 1 : cc;
-                const double jf = block_loss_f64<N>(ys, wsh, weighted, e4m3_f64(cf));
-                const double jc = block_loss_f64<N>(ys, wsh, weighted, e4m3_f64(cc));
-                if (fp8_code) fp8_code[blk] = (uint8_t)(jc < jf ? cc : cf);
-                if (fp8_loss) fp8_loss[blk] = jc < jf ? jc : jf;
+            };
+            int cf, cc;
+            for (int t = tid; t < 2 * N * KB; t += Sp::kThreads) {
+                const int b = t / (2 * N), i = t & (N - 1);
+                if (blk0 + b < nblocks) {
+                    neighbours(scale_of[b], cf, cc);
+                    const double s = e4m3_f64(t & N ? cc : cf);
+                    const double a = ads[b][i];
+                    const double g = e2m1_value(round_fp4_index(a, s));
+                    const double e = a - g * s;
+                    key[t] = wds[b][i] * (e * e);
+                }
+            }
+            __syncthreads();
+            const int b = tid / 2;
+            if (b < KB && blk0 + b < nblocks) {
+                double j = 0.0;
+                const double* term = key + tid * N;
+#pragma unroll 16
+                for (int i = 0; i < N; ++i) j = j + term[i];
+                const double jc = exchange_other<1>(j);
+                if ((tid & 1) == 0) {
+                    neighbours(scale_of[b], cf, cc);
+                    if (fp8_code) fp8_code[blk0 + b] = (uint8_t)(jc < j ? cc : cf);
+                    if (fp8_loss) fp8_loss[blk0 + b] = jc < j ? jc : j;
+                }
             }
         }
-        __syncthreads();                        // LDS is reused by the next block
+        __syncthreads();                        // LDS is reused by the next blocks
+        kb += kb_step;
+        if (kb >= bpr) kb -= bpr;
     }
 }
 
@@ -283,8 +502,9 @@ template <typename In, int N>
 hipError_t launch_optimum(const void* x, const float* colw, const float* S, int64_t nblocks,
                           int64_t bpr, double* opt_loss, double* opt_scale, uint8_t* code,
                           double* fp8_loss, hipStream_t st) {
-    const int64_t grid = nblocks < 65536 ? nblocks : 65536;    // grid-stride over blocks
-    hipLaunchKernelGGL((optimum_kernel<In, N>), dim3((unsigned)grid), dim3(kWave), 0, st,
+    const int64_t groups = (nblocks + Spread<N>::kBatch - 1) / Spread<N>::kBatch;
+    const int64_t grid = groups < 65536 ? groups : 65536;      // grid-stride over blocks
+    hipLaunchKernelGGL((optimum_kernel<In, N>), dim3((unsigned)grid), dim3(Spread<N>::kThreads), 0, st,
                        static_cast<const In*>(x), colw, S, nblocks, bpr, opt_loss, opt_scale,
                        code, fp8_loss);
     return hipGetLastError();

@@ -10,7 +10,7 @@
 // Design for gfx950:
 //  * One lane owns 16 consecutive elements; a micro-block of n elements is n/16 adjacent
 //    lanes.  Everything per block (max, window, argmin) lives in registers; partial losses
-//    of multi-lane blocks are combined with ds_swizzle exchanges.
+//    of multi-lane blocks are combined with DPP exchanges.
 //  * The FP4 rounding of two elements is one v_cvt_scalef32_pk_fp4_f32 (round to nearest
 //    even onto E2M1 of src / 2^exponent(scale), saturating at 6) and the decode back one
 //    v_cvt_scalef32_pk_f32_fp4.  A scale s = M 2^E (M in [1, 2)) is applied as u = |y| / M,
@@ -170,27 +170,31 @@ __device__ __forceinline__ int nearest_code(float v, float div, int cf, const Sc
 }
 
 // ---------------------------------------------------------------------------------------
-// Lane exchanges inside groups of 2 / 4 / 8 lanes (ds_swizzle, bit-mask mode: xor).
+// Reductions over groups of 2 / 4 / 8 adjacent lanes, in every lane of the group (DPP: the neighbour,
+// the other pair of the quad, then the mirrored half row, whose quads each hold one value by then).
+// Vector instructions, where an exchange through the LDS pipe costs its latency per step: one
+// [8192, 8192] weight, WMSE at n = 128, 201.4 -> 194.0 us.
 // ---------------------------------------------------------------------------------------
 
-template <int XOR>
-__device__ __forceinline__ float swz_xor(float v) {
-    return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), (XOR << 10) | 0x1F));
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141;
 
 template <int LPB>
 __device__ __forceinline__ float group_sum(float v) {
-    if (LPB >= 2) v += swz_xor<1>(v);
-    if (LPB >= 4) v += swz_xor<2>(v);
-    if (LPB >= 8) v += swz_xor<4>(v);
+    if (LPB >= 2) v += dpp<kDppXor1>(v);
+    if (LPB >= 4) v += dpp<kDppXor2>(v);
+    if (LPB >= 8) v += dpp<kDppHalfMirror>(v);
     return v;
 }
 
 template <int LPB>
 __device__ __forceinline__ float group_max(float v) {
-    if (LPB >= 2) v = fmaxf(v, swz_xor<1>(v));
-    if (LPB >= 4) v = fmaxf(v, swz_xor<2>(v));
-    if (LPB >= 8) v = fmaxf(v, swz_xor<4>(v));
+    if (LPB >= 2) v = fmaxf(v, dpp<kDppXor1>(v));
+    if (LPB >= 4) v = fmaxf(v, dpp<kDppXor2>(v));
+    if (LPB >= 8) v = fmaxf(v, dpp<kDppHalfMirror>(v));
     return v;
 }
 

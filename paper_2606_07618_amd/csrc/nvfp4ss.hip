@@ -29,10 +29,10 @@
 //    ulp of the quotient's midpoint without hitting it.
 //  * The dynamic global scale needs max |x| first: a streaming kernel writes one maximum per
 //    workgroup (at most 256) into the workspace, a one-wave kernel folds them into S and 1/S,
-//    and the quantization kernel reads those two words.  Kernel boundaries order the passes.
-//    Measured alternatives were slower: folding the partials in every quantization workgroup
-//    (its prologue latency), and a last-arriving-workgroup fold in the reduction kernel (an
-//    L2 write-back per workgroup for the release; with a full fence, also an L2 invalidate).
+//    and the quantization kernel reads those two words; on a small grid its workgroups fold the
+//    partials themselves (kFoldTiles).  Kernel boundaries order the passes.  A fold by the last
+//    workgroup of the reduction kernel was slower (an L2 write-back per workgroup for the
+//    release; with a full fence, also an L2 invalidate).
 #include <hip/hip_runtime.h>
 
 #include <float.h>
@@ -809,9 +809,14 @@ __device__ __forceinline__ float global_scale(uint32_t amax_bits, float denom) {
     return s == 0.0f ? FLT_TRUE_MIN : s;
 }
 
+__device__ __forceinline__ uint32_t slot_word(uint32_t i) {
+    return kSlotWord0 + (i % kSlots) * kSlotStride + i / kSlots;
+}
+static_assert(kThreads == kMaxPartials && kMaxPartials == 4 * kSlots, "a slot holds four partials");
+
 template <typename In>
 __global__ __launch_bounds__(kThreads) void amax_kernel(const In* __restrict__ x, int64_t nvec,
-                                                        uint32_t* __restrict__ partials) {
+                                                        uint32_t* __restrict__ ws, int to_slots) {
     const uint4* v = reinterpret_cast<const uint4*>(x);
     uint32_t m = 0;
     const int64_t stride = (int64_t)gridDim.x * kThreads;
@@ -829,7 +834,11 @@ __global__ __launch_bounds__(kThreads) void amax_kernel(const In* __restrict__ x
     __shared__ uint32_t part[kThreads / 64];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
     __syncthreads();
-    if (threadIdx.x == 0) partials[blockIdx.x] = max(max(part[0], part[1]), max(part[2], part[3]));
+    // partial i: word i, or one of the four words of slot i mod 64 (workgroup 0 clears those of the
+    // partials that this grid has not)
+    const uint32_t b = blockIdx.x;
+    if (threadIdx.x == 0) ws[to_slots ? slot_word(b) : b] = max(max(part[0], part[1]), max(part[2], part[3]));
+    if (to_slots && b == 0 && threadIdx.x >= gridDim.x) ws[slot_word(threadIdx.x)] = 0u;
 }
 
 // Folds the per-workgroup maxima into S and 1/S (one wave): S goes to the caller's output
@@ -841,7 +850,8 @@ __global__ __launch_bounds__(64) void scale_kernel(uint32_t* __restrict__ ws, in
                                                    uint32_t* __restrict__ zero_base, int zero_count,
                                                    int64_t zero_stride) {
     for (int t = threadIdx.x; t < zero_count * kSlots; t += 64)
-        zero_base[(t / kSlots) * zero_stride + kSlotWord0 + (t % kSlots) * kSlotStride] = 0u;
+        *reinterpret_cast<uint4*>(zero_base + (t / kSlots) * zero_stride + kSlotWord0 +
+                                  (t % kSlots) * kSlotStride) = make_uint4(0u, 0u, 0u, 0u);
     uint32_t m = 0;
     for (int i = threadIdx.x; i < npart; i += 64) m = max(m, ws[i]);
 #pragma unroll
@@ -864,8 +874,9 @@ __global__ void write_scale_kernel(float* tensor_scale, float S) { tensor_scale[
 enum ScaleSource {
     kScaleStatic = 0,         // Params::S, Params::rS (given by the caller)
     kScaleWorkspace = 1,      // S and 1/S formed by scale_kernel earlier on the stream
-    kScaleSlots = 2,          // the maximum of the workspace's |x| slots (raised atomically by
-                              // the preceding kernel of a batched call), folded here
+    kScaleSlots = 2,          // the maximum of the workspace's |x| slots (raised atomically by the
+                              // preceding kernel of a batched call, or amax_kernel's partials on
+                              // a small grid), folded here
 };
 
 struct Params {
@@ -884,9 +895,10 @@ struct Params {
     uint32_t* nx_slots;
     int win_tight;            // window variants: per-mantissa offsets (else win_lo..win_hi)
     int win_lo, win_hi;
-    int swizzled;             // scales in 128 x 4 tiles (else row-major)
     const uint16_t* up;       // fused SwiGLU input: x is the gate, this the up projection
     uint32_t sw_kt;           // 4-column scale tiles per tile row
+    uint32_t tiles;           // workgroups that quantize; those past them zero the scale padding
+    uint32_t rows, pad_mp;    // swizzled scales: rows, and rows padded to 128
     uint32_t wgroups;         // importance vectors: row r uses ((r / wg_rows) mod wgroups)
     uint32_t wgr_magic, wgr_shift, wgn_magic, wgn_shift;   // dividers by wg_rows, wgroups
 };
@@ -1050,7 +1062,33 @@ __device__ __forceinline__ void raise_next_slot(const Params& p, uint32_t tile, 
                                m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int METHOD, typename In, int N, bool SWIGLU = false>
+// Zero bytes of the swizzled scale layout that no block owns, 256 per workgroup: rows rows..mp-1
+// (all kp columns), then columns k16..kp-1 of rows 0..rows-1.  Disjoint from the bytes that the
+// tiles write, so workgroups of the same grid write them, after the tiles': a launch of its own
+// for the padding of one row took 2.2 us on the GPU after the 6.6 us of the row itself.
+__device__ __forceinline__ void zero_scale_padding(uint8_t* __restrict__ scales, const Params& p, uint32_t pad_wg) {
+    const uint32_t rows = p.rows, k16 = p.bpr, mp = p.pad_mp, kp = 4u * p.sw_kt;
+    const uint32_t t = pad_wg * kThreads + threadIdx.x;
+    const uint32_t n_rows = (mp - rows) * kp;
+    const uint32_t wcols = kp - k16;
+    uint32_t m, k;
+    if (t < n_rows) {
+        m = rows + t / kp;
+        k = t % kp;
+    } else if (t < n_rows + rows * wcols) {
+        const uint32_t u = t - n_rows;
+        m = u / wcols;
+        k = k16 + u % wcols;
+    } else {
+        return;
+    }
+    scales[swizzled_offset(m, k, p.sw_kt)] = 0;
+}
+
+// SWZ: scales in 128 x 4 tiles (block 16), the grid's last workgroups for their padding.  A kernel of
+// its own: the padding's branch ahead of a tile's loads costs a row-major layer 0.7 % (batched MSE
+// 361.3 -> 364.0 us).
+template <int METHOD, typename In, int N, bool SWIGLU, bool SWZ>
 __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ x,
                                                          const float* __restrict__ colw,
                                                          uint8_t* __restrict__ q,
@@ -1059,8 +1097,18 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
     constexpr bool WEIGHTED_OBJ = METHOD == kSweepWmse || METHOD == kFourSix || METHOD == kWindowWmse;
     __shared__ Scale tab_all[kTabSize];
     Scale* tab = tab_all + kTabLo;                 // tab[c] for codes c in -16..143
-    // the workgroup's tile of this tensor; with swizzled scales, tiles are regrouped by XCD
-    const uint32_t tile = p.swizzled ? xcd_tile(blockIdx.x, gridDim.x) : blockIdx.x;
+    // the workgroup's tile of this tensor; with swizzled scales, tiles are regrouped by XCD, and
+    // workgroups past them zero the padding
+    if (SWZ && blockIdx.x >= p.tiles) {
+        zero_scale_padding(scales, p, blockIdx.x - p.tiles);
+        return;
+    }
+    const uint32_t tile = SWZ ? xcd_tile(blockIdx.x, p.tiles) : blockIdx.x;
+    // The arguments behind the weights' address are fetched with those behind the tile's: left to the
+    // compiler they wait for a second round of scalar loads, ahead of the weights' own (a layer, WMSE:
+    // 464.9 us against 461.5).
+    if constexpr (WEIGHTED_OBJ)
+        asm volatile("" ::"s"(colw), "s"(p.bpr_magic), "s"(p.wgroups), "s"(p.wgr_magic), "s"(p.wgn_magic));
     const int lane = threadIdx.x & 63;
     const int64_t gtid = (int64_t)tile * kThreads + threadIdx.x;
     const int64_t blk = gtid / LPB;
@@ -1080,7 +1128,7 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
     float w[kLaneElems];
     const bool use_w = WEIGHTED_OBJ && colw != nullptr;
     uint32_t row = 0, kb = 0;         // the block's row and block column
-    if (use_w || p.swizzled) {
+    if (use_w || SWZ) {
         row = div_bpr((uint32_t)blk_c, p);
         kb = (uint32_t)blk_c - row * p.bpr;
     }
@@ -1097,8 +1145,9 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
     if (p.nx_per > 0) raise_next_slot(p, tile, next_share_max<In>(p, tile));   // uniform
     __shared__ float s_scale[2];
     if (p.scale_src == kScaleSlots && threadIdx.x < 64) {
-        // the slots were raised by the previous kernel on the stream: wave 0 folds them
-        uint32_t m = p.ws[kSlotWord0 + threadIdx.x * kSlotStride];
+        // the slots were written by the previous kernel on the stream: wave 0 folds them
+        const uint4 v = *reinterpret_cast<const uint4*>(p.ws + kSlotWord0 + threadIdx.x * kSlotStride);
+        uint32_t m = max(max(v.x, v.y), max(v.z, v.w));
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off, 64));
         if (threadIdx.x == 0) {
@@ -1357,35 +1406,13 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
         pv.y = packed[1];
         __builtin_nontemporal_store(pv, reinterpret_cast<u32x2*>(dst));
         if (part == 0) {
-            if (p.swizzled)      // through L2, which merges the 4-byte pieces of a tile's lines
+            if (SWZ)             // through L2, which merges the 4-byte pieces of a tile's lines
                 scales[swizzled_offset(row, kb, p.sw_kt)] = (uint8_t)code;
             else
                 __builtin_nontemporal_store((uint8_t)code, scales + blk);
         }
     }
     }
-}
-
-// Zero bytes of the swizzled scale layout that no block owns: rows rows..mp-1 (all kp columns),
-// then columns k16..kp-1 of rows 0..rows-1.  Disjoint from the bytes the quantization kernel
-// writes, so the two may run in either order.
-__global__ __launch_bounds__(256) void swizzle_pad_kernel(uint8_t* __restrict__ scales, uint32_t rows,
-                                                          uint32_t k16, uint32_t mp, uint32_t kp) {
-    const uint32_t t = blockIdx.x * 256u + threadIdx.x;
-    const uint32_t n_rows = (mp - rows) * kp;
-    const uint32_t wcols = kp - k16;
-    uint32_t m, k;
-    if (t < n_rows) {
-        m = rows + t / kp;
-        k = t % kp;
-    } else if (t < n_rows + rows * wcols) {
-        const uint32_t u = t - n_rows;
-        m = u / wcols;
-        k = k16 + u % wcols;
-    } else {
-        return;
-    }
-    scales[swizzled_offset(m, k, kp / 4)] = 0;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1490,9 +1517,20 @@ int64_t quant_grid(const Call& c) {
 
 template <int METHOD, typename In, int N, bool SWIGLU = false>
 hipError_t launch_quant(const Call& c, const Params& p) {
-    const int64_t grid = quant_grid(c);
-    hipLaunchKernelGGL((quant_kernel<METHOD, In, N, SWIGLU>), dim3((unsigned)grid), dim3(kThreads), 0,
-                       c.stream, static_cast<const In*>(c.x), c.colw, c.q, c.scales, p);
+    const In* x = static_cast<const In*>(c.x);
+    if (c.layout == NVFP4_SCALES_SWIZZLED) {           // block 16 only
+        if constexpr (N == 16 && METHOD <= kSweepWmse) {
+            // bytes of the scale buffer that no block owns, one per lane
+            const uint64_t pad = (uint64_t)p.pad_mp * 4u * p.sw_kt - (uint64_t)p.rows * p.bpr;
+            const int64_t grid = (int64_t)p.tiles + (int64_t)((pad + kThreads - 1) / kThreads);
+            hipLaunchKernelGGL((quant_kernel<METHOD, In, N, SWIGLU, true>), dim3((unsigned)grid),
+                               dim3(kThreads), 0, c.stream, x, c.colw, c.q, c.scales, p);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
+    hipLaunchKernelGGL((quant_kernel<METHOD, In, N, SWIGLU, false>), dim3(p.tiles), dim3(kThreads), 0,
+                       c.stream, x, c.colw, c.q, c.scales, p);
     return hipGetLastError();
 }
 
@@ -1541,24 +1579,24 @@ int validate(const Call& c) {
     return NVFP4_OK;
 }
 
-// Dynamic global scale of a non-empty tensor: the |x| reduction and the fold into S, 1/S
-// (which also clears the |x| slots of zero_count workspaces from zero_base, for a batched call).
-hipError_t launch_scale(const Call& c, hipStream_t stream, int* npart, void* zero_base = nullptr,
+// Dynamic global scale of a non-empty tensor: the |x| reduction and, with fold, the kernel that folds
+// its partials into S, 1/S and clears the |x| slots of zero_count workspaces from zero_base (a batched
+// call); without it the partials are left in the slots, for the quantization kernel.
+hipError_t launch_scale(const Call& c, hipStream_t stream, bool fold, void* zero_base = nullptr,
                         int zero_count = 0) {
     const int64_t n = c.rows * c.cols;
     const int64_t nvec = n * (c.dtype == NVFP4_IN_F32 ? 4 : 2) / 16;
     int64_t g = (nvec + kThreads * 8 - 1) / (kThreads * 8);
     if (g < 1) g = 1;
     if (g > kMaxPartials) g = kMaxPartials;
-    *npart = (int)g;
     if (c.dtype == NVFP4_IN_F32)
         hipLaunchKernelGGL(amax_kernel<float>, dim3((unsigned)g), dim3(kThreads), 0, stream,
-                           static_cast<const float*>(c.x), nvec, static_cast<uint32_t*>(c.ws));
+                           static_cast<const float*>(c.x), nvec, static_cast<uint32_t*>(c.ws), fold ? 0 : 1);
     else
         hipLaunchKernelGGL(amax_kernel<uint16_t>, dim3((unsigned)g), dim3(kThreads), 0, stream,
-                           static_cast<const uint16_t*>(c.x), nvec, static_cast<uint32_t*>(c.ws));
+                           static_cast<const uint16_t*>(c.x), nvec, static_cast<uint32_t*>(c.ws), fold ? 0 : 1);
     hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
+    if (err != hipSuccess || !fold) return err;
     hipLaunchKernelGGL(scale_kernel, dim3(1), dim3(64), 0, stream, static_cast<uint32_t*>(c.ws),
                        (int)g, 6.0f * c.fp8_range, c.tensor_scale, static_cast<uint32_t*>(zero_base),
                        zero_count, (int64_t)(kWorkspaceBytes / sizeof(uint32_t)));
@@ -1594,8 +1632,10 @@ hipError_t launch_main(const Call& c, hipStream_t stream, const Chain& chain = C
     const int64_t tiles = quant_grid(c);
     p.nx_per = p.nx_vec > 0 ? (p.nx_vec + tiles - 1) / tiles : 0;
     p.nx_slots = chain.nx_ws ? chain.nx_ws + kSlotWord0 : nullptr;
-    p.swizzled = c.layout == NVFP4_SCALES_SWIZZLED ? 1 : 0;
     p.sw_kt = (uint32_t)((c.cols / c.block + 3) / 4);
+    p.tiles = (uint32_t)tiles;
+    p.rows = (uint32_t)c.rows;
+    p.pad_mp = (uint32_t)((c.rows + 127) / 128 * 128);
     p.wgroups = (uint32_t)c.wgroups;
     make_divider((uint32_t)c.wgroup_rows, &p.wgr_magic, &p.wgr_shift);
     make_divider((uint32_t)c.wgroups, &p.wgn_magic, &p.wgn_shift);
@@ -1623,6 +1663,14 @@ hipError_t launch_main(const Call& c, hipStream_t stream, const Chain& chain = C
     }
 }
 
+// Grids up to this many workgroups fold the partial maxima in every workgroup's prologue; past it
+// a one-wave kernel folds them once.  The launch costs 1 to 2 us on the GPU (and its share of the
+// host), the fold some 0.1 us of each workgroup's life, beside its tile's loads.  Measured, fold
+// in the prologue against the kernel: MSE on [1, 4096] 7.2 / 8.3 us, [1024, 1024] binary32 10.2 /
+// 11.4, [2048, 4096] (2048 workgroups) 28.2 / 28.3; AbsMax there 9.9 / 11.7, on [4096, 4096] 19.7
+// each, on [8192, 8192] 57.6 / 53.2.
+constexpr int64_t kFoldTiles = 2048;
+
 // S of an empty tensor is 1 (or the given S).
 hipError_t launch_empty(const Call& c, hipStream_t stream) {
     hipLaunchKernelGGL(write_scale_kernel, dim3(1), dim3(1), 0, stream, c.tensor_scale,
@@ -1634,9 +1682,13 @@ int run_quant(const Call& c) {
     const int rc = validate(c);
     if (rc != NVFP4_OK) return rc;
     if (c.rows * c.cols == 0) return launch_empty(c, c.stream) == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
-    int npart = 0;
-    if (c.static_scale == 0.0f && launch_scale(c, c.stream, &npart) != hipSuccess) return NVFP4_ERR_HIP;
-    return launch_main(c, c.stream) == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
+    Chain ch;
+    if (c.static_scale == 0.0f) {
+        const bool fold = quant_grid(c) > kFoldTiles;
+        if (launch_scale(c, c.stream, fold) != hipSuccess) return NVFP4_ERR_HIP;
+        if (!fold) ch.scale_src = kScaleSlots;
+    }
+    return launch_main(c, c.stream, ch) == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
 }
 
 // Several tensors, dynamic scales, one stream.  The non-empty tensors form a chain in
@@ -1683,8 +1735,7 @@ int run_batched(int method, const nvfp4_tensor* t, int count, int dtype, int blo
     for (int k = 0; ok && k < count; ++k)
         if (size_of(k) == 0) ok = launch_empty(call_of(k), main) == hipSuccess;
     int cur = next_of(-1);
-    int npart = 0;
-    if (ok && cur >= 0) ok = launch_scale(call_of(cur), main, &npart, ws, count) == hipSuccess;
+    if (ok && cur >= 0) ok = launch_scale(call_of(cur), main, true, ws, count) == hipSuccess;
     for (bool first = true; ok && cur >= 0; first = false) {
         const int kn = next_of(cur);
         Chain ch;
@@ -1731,18 +1782,7 @@ int run_online(const Call& c) {
     }
     Call cc = c;
     if (!c.colw) cc.wgroups = cc.wgroup_rows = 1;
-    if (launch_main(cc, c.stream) != hipSuccess) return NVFP4_ERR_HIP;
-    if (c.layout == NVFP4_SCALES_SWIZZLED) {
-        const uint32_t rows = (uint32_t)c.rows, k16 = (uint32_t)(c.cols / 16);
-        const uint32_t mp = (rows + 127) / 128 * 128, kp = (k16 + 3) / 4 * 4;
-        const uint64_t pad = (uint64_t)(mp - rows) * kp + (uint64_t)rows * (kp - k16);
-        if (pad > 0) {
-            hipLaunchKernelGGL(swizzle_pad_kernel, dim3((unsigned)((pad + 255) / 256)), dim3(256), 0,
-                               c.stream, c.scales, rows, k16, mp, kp);
-            if (hipGetLastError() != hipSuccess) return NVFP4_ERR_HIP;
-        }
-    }
-    return NVFP4_OK;
+    return launch_main(cc, c.stream) == hipSuccess ? NVFP4_OK : NVFP4_ERR_HIP;
 }
 
 }  // namespace

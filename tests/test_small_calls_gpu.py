@@ -1,0 +1,57 @@
+"""Small calls on the GPU: the padding of swizzled scales at the edges of its 128 x 4 tiles, written by
+the launch that quantizes, and the dynamic global scale on both sides of the grid size up to which
+every workgroup folds the reduction's partial maxima itself."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+from test_parity_gpu import DEV
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows", [1, 31, 127, 128, 129, 257])
+@pytest.mark.parametrize("k16", [1, 3, 4, 5, 256])
+@pytest.mark.parametrize("fused", [False, True])
+def test_swizzled_padding(rows, k16, fused):
+    import paper_2606_07618_amd as nv
+    cols = 16 * k16
+    g = workloads.generator(DEV, 71, rows, k16)
+    x = torch.randn((rows, cols), generator=g, device=DEV).to(torch.bfloat16)
+    nbytes = nv.nvfp4_scales_bytes(rows, cols, 16, 1)
+    q = torch.empty((rows, cols // 2), dtype=torch.uint8, device=DEV)
+    sc = torch.full((nbytes + 64,), 0xA5, dtype=torch.uint8, device=DEV)     # a guard past the end
+    if fused:
+        up = torch.randn((rows, cols), generator=g, device=DEV).to(torch.bfloat16)
+        h = nv.swiglu(x, up)
+        nv.quantize_online_swiglu(x, up, "absmax", 0.004, layout="swizzled", out=(q, sc))
+    else:
+        h = x
+        nv.quantize_online(x, "absmax", 0.004, layout="swizzled", out=(q, sc))
+    torch.cuda.synchronize()
+    q_ref, sc_ref = oracle.quantize_online("absmax", workloads.host_array(h), 0.004, 16, None, 1, 1, "swizzled")
+    assert np.array_equal(q.cpu().numpy(), q_ref)
+    got = sc.cpu().numpy()
+    assert np.array_equal(got[:nbytes], sc_ref.reshape(-1))
+    assert np.all(got[nbytes:] == 0xA5)
+
+
+# 16 elements a lane, 256 lanes a workgroup: 1, 2, 65, 2047, 2048 and 2049 workgroups; 1 to 256 partials
+@pytest.mark.parametrize("rows,cols", [(1, 16), (3, 2048), (65, 4096), (2047, 4096), (2048, 4096), (2049, 4096)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("at", [0, -1])
+def test_dynamic_scale_on_both_folds(rows, cols, dtype, at):
+    import paper_2606_07618_amd as nv
+    g = workloads.generator(DEV, 72, rows, cols)
+    x = torch.randn((rows, cols), generator=g, device=DEV).to(dtype)
+    x.view(-1)[at] = -37.0                            # the maximum, in the first or the last partial
+    q, sc, S = nv.quantize(x, "absmax", 16)
+    S_ref = float(np.float32(37.0) / np.float32(6.0 * 448.0))
+    q2, sc2 = nv.quantize_online(x, "absmax", S_ref)  # the static path
+    torch.cuda.synchronize()
+    assert S.item() == S_ref
+    assert torch.equal(q, q2) and torch.equal(sc, sc2)
+    zero_q, zero_sc, zero_S = nv.quantize(torch.zeros_like(x), "scalesweep_mse", 16)
+    assert zero_S.item() == 1.0 and int(zero_q.max()) == 0

@@ -68,6 +68,7 @@ constexpr float kBand = 0x1p-14f;
 constexpr float kBandAbs = 0x1p-120f;
 
 typedef float float2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------------------------------
@@ -249,6 +250,14 @@ __device__ __forceinline__ void load_weights(const float* p, float (&w)[kLaneEle
     }
 }
 
+// max(|a|, |b|, c) in one instruction (abs source modifiers); c >= 0.  The inputs come from
+// arithmetic, so none is a signaling NaN and no canonicalization is needed.
+__device__ __forceinline__ float max3_abs(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, |%1|, |%2|, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
 // ---------------------------------------------------------------------------------------
 // SwiGLU producer of the fused online quantizer: h = bf16(RN(silu(g) * u)).
 // ---------------------------------------------------------------------------------------
@@ -283,13 +292,56 @@ __device__ __forceinline__ uint32_t swiglu_bf16(float g, float u) {
     return (b + 0x7FFFu + ((b >> 16) & 1u)) >> 16;
 }
 
-// The 16 producer outputs of one lane (bfloat16 values widened to binary32, exactly).
+// RN(g / RN(1 + e^-g)) for |g| < 80, the same bits as above.  There the exponential needs no clamp,
+// 2^n is an addition to the exponent field (n is read from the low bits of the sum that rounds
+// it), and the division is a product with the refined reciprocal and one remainder step: the
+// remainder is exact, since nothing in it underflows (below 2^-25 the divisor is 2 and the
+// quotient exact itself).  All 34,112 such g agree with the division.
+__device__ __forceinline__ float silu_in_range(float g) {
+    const float t = -g * 0x1.715476p+0f + 0x1.8p23f;
+    const float n = t - 0x1.8p23f;
+    float r = fmaf(-n, 0x1.62e4p-1f, -g);
+    r = fmaf(-n, 0x1.7f7d1cp-20f, r);
+    float q = 0x1.6c16c2p-10f;
+    q = fmaf(q, r, 0x1.111112p-7f);
+    q = fmaf(q, r, 0x1.555556p-5f);
+    q = fmaf(q, r, 0x1.555556p-3f);
+    q = fmaf(q, r, 0.5f);
+    q = fmaf(q, r, 1.0f);
+    q = fmaf(q, r, 1.0f);
+    const float d = 1.0f + __uint_as_float(__float_as_uint(q) + (__float_as_uint(t) << 23));
+    float rd = __builtin_amdgcn_rcpf(d);
+    rd = fmaf(fmaf(-d, rd, 1.0f), rd, rd);
+    const float q0 = g * rd;
+    return fmaf(-fmaf(q0, d, -g), rd, q0);        // in this form a zero keeps its sign
+}
+
+// The 16 producer outputs of one lane (bfloat16 values widened to binary32, exactly).  Bound by
+// vector instructions: about 25 an element where every gate of the lane is in range, against 37 in
+// the general form (a range test, a division and a rounding by integers for each element).
+// Fused, [8192, 14336], before and after: AbsMax 132.4 -> 110.3 us, four-over-six 164.8 -> 137.7,
+// MSE 228.9 -> 223.6, WMSE 278.0 -> 259.9.
 __device__ __forceinline__ void swiglu_lane(const uint16_t* gate, const uint16_t* up, float (&h)[kLaneElems]) {
     float g[kLaneElems], u[kLaneElems];
     Loader<uint16_t>::load(gate, g);
     Loader<uint16_t>::load(up, u);
+    float gmax = 0.f;
 #pragma unroll
-    for (int i = 0; i < kLaneElems; ++i) h[i] = __uint_as_float(swiglu_bf16(g[i], u[i]) << 16);
+    for (int i = 0; i < kLaneElems; i += 2) gmax = max3_abs(g[i], g[i + 1], gmax);
+    if (gmax < 80.0f) {
+#pragma unroll
+        for (int i = 0; i < kLaneElems; i += 2) {
+            float2v v;
+            v.x = silu_in_range(g[i]) * u[i];
+            v.y = silu_in_range(g[i + 1]) * u[i + 1];
+            const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));   // RNE
+            h[i] = __uint_as_float(b << 16);
+            h[i + 1] = __uint_as_float(b & 0xFFFF0000u);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kLaneElems; ++i) h[i] = __uint_as_float(swiglu_bf16(g[i], u[i]) << 16);
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -710,14 +762,6 @@ __device__ __forceinline__ void pruned_wmse_losses(const float (&y)[kLaneElems],
     for (int d = 0; d < kLow; ++d)
         J[d] = d >= dk ? __uint_as_float(mine[t + (uint32_t)(kLow - 1 - d)]) : __builtin_inff();
     J[kTop] = keep_top ? __uint_as_float(mine[0]) : __builtin_inff();
-}
-
-// max(|a|, |b|, c) in one instruction (abs source modifiers); c >= 0.  The inputs come from
-// arithmetic, so none is a signaling NaN and no canonicalization is needed.
-__device__ __forceinline__ float max3_abs(float a, float b, float c) {
-    float r;
-    asm("v_max3_f32 %0, |%1|, |%2|, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
 }
 
 // Exactly rounded u = RN32(v / M) for M in [1, 2) with rM = RN32(1 / M) (Markstein): the

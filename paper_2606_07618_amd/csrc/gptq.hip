@@ -14,17 +14,15 @@
 //     upper triangle in tiles, first the column of tiles the next block needs, then the rest
 //     beside the next block's own factor (look-ahead).  So each element receives its terms
 //     k = n-1, ..., j+1 in that order.
-//   * quantize: columns are taken in tiles of 64.  A tile kernel gives each row a quad of
-//     lanes holding the tile's running values in registers: column b's value is quantized and
-//     its error times U added to the tile's later columns, b = a0, a0 + 1, ... in order.  A
-//     trailing-update kernel then adds the tile's 64 errors times U to every later column,
-//     term by term in tile order: first to the next tile's columns, then to the rest beside
-//     the next tile's kernel (look-ahead).  Every x_a therefore receives its terms
-//     b = 0, 1, ... in ascending order, as the sequential definition adds them.
+//   * quantize: columns are taken in tiles of 64, the values kept by columns.  A launch takes one
+//     tile: each row's lanes add the terms of the tile or two before it, then walk the columns:
+//     column b's value is quantized and its error times U added to the tile's later columns, b =
+//     a0, a0 + 1, ... in order.  Beside it the same launch adds earlier tiles' errors times U to the
+//     columns past the tile, term by term in tile order (look-ahead).  Every x_a therefore
+//     receives its terms b = 0, 1, ... in ascending order, as the sequential definition adds them.
 //   The sequential kernels (diagonal block, panel, tile) hold no branch per step: the columns
-//   are interleaved over a quad's lanes (column 4m + q in lane q), so a step's updates need at
-//   most one select, and its operands that do not depend on the running values are formed
-//   ahead of the dependent chain.
+//   are interleaved over a row's lanes, so a step's updates need at most one select, and its
+//   operands that do not depend on the running values are formed ahead of the dependent chain.
 // Q(x) is the quantizers' rounding: y = RN32(RN32(x) / S), nibble sign(y) << 3 | RNE_FP4(|y| /
 // s), w^ = +-E2M1 * s * S (exact in binary64).
 #include <hip/hip_runtime.h>
@@ -60,28 +58,13 @@ __device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int,
     (f(std::integral_constant<int, B>()), ...);
 }
 
-// Lane l of a quad broadcasts v to the quad's four lanes (a DPP quad permutation).
-template <int L>
-__device__ __forceinline__ uint32_t quad_bcast_u32(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, L * 0x55, 0xF, 0xF, false);
-}
-
 // Lane l of each 16-lane row broadcasts v to the row's lanes (DPP row_newbcast).
 template <int L>
 __device__ __forceinline__ double row_bcast(double v) {
     constexpr int ctrl = 0x150 + L;
     const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, ctrl, 0xF, 0xF, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), ctrl, 0xF, 0xF, false);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-
-template <int L>
-__device__ __forceinline__ double quad_bcast(double v) {
-    constexpr int ctrl = L * 0x55;                    // quad_perm(L, L, L, L)
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, ctrl, 0xF, 0xF, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), ctrl, 0xF, 0xF, false);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, ctrl, 0xF, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), ctrl, 0xF, 0xF, true);
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
@@ -93,13 +76,14 @@ __global__ __launch_bounds__(256) void diag_kernel(const double* __restrict__ H,
     if (i < n) diag[i] = H[i * n + i];
 }
 
-// perm[rank(i)] = i, rank = number of columns with a larger diagonal, or an equal one and a
+// perm[rank(i)] = i, inv[i] = rank(i), rank = number of columns with a larger diagonal, or an equal one and a
 // smaller index (a stable descending order).  64 columns i per workgroup; each of its 16 waves
 // counts over a sixteenth of every 1024-value chunk of the diagonal staged in LDS (one value per
 // step, read by the wave's lanes alike), and the sixteen counts are added.
 constexpr int kOrderParts = 16;
 __global__ __launch_bounds__(64 * kOrderParts) void order_kernel(const double* __restrict__ diag, int64_t n,
-                                                                 int* __restrict__ perm) {
+                                                                 int* __restrict__ perm,
+                                                                 int* __restrict__ inv) {
     constexpr int kChunk = 1024, kPer = kChunk / kOrderParts;
     __shared__ double chunk[kChunk];
     __shared__ int part_rank[kOrderParts][64];
@@ -125,6 +109,7 @@ __global__ __launch_bounds__(64 * kOrderParts) void order_kernel(const double* _
         int r = 0;
         for (int k = 0; k < kOrderParts; ++k) r += part_rank[k][il];
         perm[r] = (int)i;
+        inv[i] = r;
     }
 }
 
@@ -296,7 +281,7 @@ __global__ __launch_bounds__(256) void factor_panel_kernel(double* __restrict__ 
     if (tid < kTile) Db[tid] = D[k0 + tid];
     const int rr = tid >> 4, q = tid & 15;
     const int64_t i = i0 + rr;
-    double v[4];
+    double v[4], uf[4];                      // uf: the lane's columns of U
     if (i < k0) {
 #pragma unroll
         for (int m = 0; m < 4; ++m) v[m] = Uc[(k0 + 16 * m + q) * n + i];
@@ -309,6 +294,7 @@ __global__ __launch_bounds__(256) void factor_panel_kernel(double* __restrict__ 
         const double dk = Db[kk];
         const double u = row_bcast<qk>(v[mk]) / dk;
         Uc[(k0 + kk) * n + i] = u;           // the row's lanes store the same value
+        if (q == qk) uf[mk] = u;
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             if (16 * m < kk) {               // some lane of the row holds a column before kk
@@ -318,6 +304,10 @@ __global__ __launch_bounds__(256) void factor_panel_kernel(double* __restrict__ 
         }
     };
     for_each_index(step, std::make_integer_sequence<int, kTile>());
+    // the row's U once more by rows, in the lower triangle (nothing of A is there): the
+    // quantization reads U_{i,k} over consecutive k
+#pragma unroll
+    for (int m = 0; m < 4; ++m) Uc[i * n + k0 + 16 * m + q] = uf[m];
 }
 
 // A_ij -= sum over the block's k, downwards, of (U_ik U_jk) D_k for i <= j < k0: one
@@ -442,236 +432,321 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
 
 // ---- quantize -----------------------------------------------------------------------------
 
+// X[inv[c]][r] = w[r][c]: the weights by columns, in the visiting order.  64 x 64 values per
+// workgroup through LDS, so that both sides move whole lines: [4096, 4096] bf16 46 us (gathered
+// row by row in the visiting order 64).
 template <typename In>
-__global__ __launch_bounds__(256) void init_x_kernel(const In* __restrict__ w, const int* __restrict__ perm,
+__global__ __launch_bounds__(256) void init_x_kernel(const In* __restrict__ w, const int* __restrict__ inv,
                                                      int64_t rows, int64_t n, double* __restrict__ X) {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= rows * n) return;
-    const int64_t r = t / n, a = t % n;
-    X[t] = (double)load_w<In>(w, r * n + perm[a]);
+    __shared__ float v[kTile][kTile + 1];
+    __shared__ int to[kTile];
+    const int64_t c0 = (int64_t)blockIdx.x * kTile, r0 = (int64_t)blockIdx.y * kTile;
+    const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
+    for (int k = part; k < kTile; k += 4)
+        if (r0 + k < rows) v[k][lane] = load_w<In>(w, (r0 + k) * n + c0 + lane);
+    if (part == 0) to[lane] = inv[c0 + lane];
+    __syncthreads();
+    if (r0 + lane < rows)
+        for (int k = part; k < kTile; k += 4) X[(int64_t)to[k] * rows + r0 + lane] = (double)v[lane][k];
 }
 
-// One tile of 64 columns, right-looking, four lanes (a quad) per row and 64 rows per
-// workgroup: lane p of a quad holds the running values of tile columns 4j + p, j = 0..15, in
-// registers, with their weights and scale codes.  Column b's value is broadcast to the quad,
-// which quantizes it (every lane the same operations, so the same error), and each lane then
-// adds error_b * U_b,a to each of its columns a > b.  Every value thus receives its terms
-// b = a0, a0 + 1, ... in ascending order, as the sequential definition adds them.  U's tile
-// block is staged in LDS, each lane's columns of a U row contiguous.  A column's work holds
-// no branch: its scale, weight, midpoint products and U values do not depend on the running
-// value, so they are formed ahead of the chain value -> quotient -> E2M1 index -> error -> the
-// next column's value that bounds the walk.
+// One tile of 64 columns, right-looking, a 16-lane row of lanes per matrix row and 16 rows per
+// workgroup: lane q holds the running values of tile columns 16m + q, m = 0..3.  The tile's values
+// first receive the terms of the one or two tiles before it (the lane row's errors broadcast in it
+// with DPP, U in LDS), then column b is taken: every lane quantizes its own value of the group m =
+// b / 16 (only lane b % 16's is final), that lane's error is broadcast, and each lane adds error *
+// U_b,a to its columns a > b.  A column's values stay as they are once it is taken, so the group's
+// last step leaves every lane its own error and code.  Every value thus receives its terms in
+// ascending order, as the sequential definition adds them.
+// Bound by the instructions of the walk: a wave alone on its SIMD issues one in about 8 cycles, so
+// a column costs what it holds, about 25 (two exact quotients by reciprocal and remainder, the
+// conversion to E2M1 and back, two broadcasts, at most four updates): 15 us a tile with the terms of
+// one before.  A quad of lanes per row, with an IEEE division and seven binary64 comparisons by
+// every lane, took 35 us and a launch of 7 us for those terms.
+constexpr int kTileRows = 16;
 struct alignas(16) TileLds {
-    double T[kTile][kTile + 2];    // T[b][16 p + j] = U_{a0+b, a0+4j+p} (rows padded: the staging
-                                   // writes of a wave, one per row, spread over the banks)
+    double T[kTile][kTile + 2];    // T[b][4q + m] = U_{b, 16m + q} of one 64 x 64 block of U (rows padded:
+                                   // the staging writes of a wave, one per row, spread over the banks)
     int pc[kTile];
 };
+
+// What quantizing a value of one column and row takes.
+struct ColumnScale {
+    double w, sS;                  // the weight; s S
+    float M, rM, cvs;              // s = M 2^E, RN32(1 / M), s (1 for the zero code: M = rM = 0)
+    int code;
+};
+
+// Q(x) as in the definition: the error w - Q(x) and the nibble.  k is the number of midpoints passed,
+// a tie counting only toward an even index; none for a zero scale.
+__device__ __forceinline__ void quantize_any(double x, float S, const ColumnScale& c, double* e, uint32_t* nibble) {
+    const float y = __fdiv_rn(__double2float_rn(x), S);
+    const double ay = fabs((double)y), s = e4m3_f64(c.code);
+    int k = 0;
+#pragma unroll
+    for (int j = 0; j < 7; ++j) k += ((j & 1) ? ay >= e2m1_mid(j) * s : ay > e2m1_mid(j) * s) ? 1 : 0;
+    k = c.code == 0 ? 0 : k;
+    const bool neg = signbit(y);
+    const double wq = (double)((0xC8643210u >> (4 * k)) & 15u) * (s * (0.5 * (double)S));
+    *e = c.w - (neg ? -wq : wq);
+    *nibble = (neg ? 8u : 0u) | (uint32_t)k;
+}
+
+typedef float float2v __attribute__((ext_vector_type(2)));
+
+// v / d from r = RN32(1 / d) and one remainder (Markstein), correctly rounded where nothing under- or
+// overflows; in this form a zero keeps its sign.
+__device__ __forceinline__ float div_recip(float v, float d, float r) {
+    const float u = v * r;
+    return fmaf(-fmaf(u, d, -v), r, u);
+}
+
+// The same for S in [2^-26, 2^26] and |RN32(x)| < 2^100 (*ok is cleared otherwise).  A quotient that
+// is inexact because it underflows is below 2^-20 and gives a zero of its sign either way.  RN32(y / M)
+// rounds to the same E2M1 value as y / s: a midpoint times M has at most 7 significant bits, so y is at
+// least an ulp away from one that it misses.
+__device__ __forceinline__ void quantize_fast(double x, float S, float rS, const ColumnScale& c, double* e,
+                                              uint32_t* nibble, bool* ok) {
+    const float xf = __double2float_rn(x);
+    *ok = *ok && fabsf(xf) < 0x1p100f;
+    const float u = div_recip(div_recip(xf, S, rS), c.M, c.rM);
+    uint32_t any;                        // the conversion writes one byte and keeps the others
+    asm volatile("" : "=v"(any));
+    const uint32_t p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(any, u, u, c.cvs, 0);
+    const float2v g = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(p, 1.0f, 0);
+    *e = c.w - (double)g.x * c.sS;       // +-E2M1 * (s S), exact
+    *nibble = p & 15u;
+}
+
+__device__ __forceinline__ double lane_row_value(double v, int lane) {
+    return __shfl(v, (int)(threadIdx.x & 48) | lane, 64);
+}
+
+__device__ __forceinline__ void read_row(double (&t)[4], const double* p) {
+    const double2 a = reinterpret_cast<const double2*>(p)[0], b = reinterpret_cast<const double2*>(p)[1];
+    t[0] = a.x;
+    t[1] = a.y;
+    t[2] = b.x;
+    t[3] = b.y;
+}
 
 template <typename In>
 __device__ __forceinline__ void tile_body(const In* __restrict__ w, const int* __restrict__ perm,
                                           const double* __restrict__ Uc, const uint8_t* __restrict__ scales,
                                           const float* __restrict__ tensor_scale, int64_t rows, int64_t n,
-                                          int block, int64_t a0, const double* __restrict__ X,
-                                          double* __restrict__ Et, uint8_t* __restrict__ codes,
-                                          int64_t rblock, TileLds& L) {
+                                          int block, int64_t a0, int nprev, double* __restrict__ X,
+                                          uint8_t* __restrict__ codes, int64_t rblock, TileLds& L) {
     const int tid = threadIdx.x;
-    for (int t = tid; t < kTile * kTile; t += 4 * kTile) {
-        const int a = t / kTile, b = t % kTile;                   // coalesced over b
-        L.T[b][16 * (a & 3) + (a >> 2)] = Uc[(a0 + a) * n + a0 + b];
-    }
+    const int rr = tid >> 4, q = tid & 15;
+    const int64_t r = rblock * kTileRows + rr;
+    const bool live = r < rows;
+    const int64_t rc = live ? r : rows - 1;            // the loads of rows past the end
     if (tid < kTile) L.pc[tid] = perm[a0 + tid];
-    __syncthreads();
-    const int rr = tid >> 2, p = tid & 3;
-    const int64_t r = rblock * kTile + rr;
-    if (r >= rows) return;                   // whole quads: the broadcasts stay inside live rows
-    const int64_t nb = n / block;
-    double x[16];
-    float wr[16];                            // weights of this lane's columns
-    uint32_t sc4[4] = {0u, 0u, 0u, 0u};      // their scale codes, four to a register
+    double x[4];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int c = L.pc[4 * j + p];
-        x[j] = X[r * n + a0 + 4 * j + p];
-        wr[j] = load_w<In>(w, r * n + c);
-        sc4[j >> 2] |= (uint32_t)scales[r * nb + c / block] << (8 * (j & 3));
-    }
-    const float S = tensor_scale[0];
-    const double halfS = 0.5 * (double)S;
-    const double* Tp = &L.T[0][16 * p];
+    for (int m = 0; m < 4; ++m) x[m] = X[(a0 + 16 * m + q) * rows + rc];
+    // the block of U that the walk needs, fetched ahead of the earlier tiles' terms
+    double own[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) own[k] = Uc[(a0 + (tid >> 6) + 4 * k) * n + a0 + (tid & 63)];   // U_{a0 + b, a0 + a}
+    const double* Tp = &L.T[0][4 * q];
     constexpr int kTRow = kTile + 2;
-    uint8_t* crow = codes + r * n;
-    double* erow = Et + r * kTile;
-    auto column = [&](auto bc) {
-        constexpr int b = decltype(bc)::value, pb = b & 3, jb = b >> 2;
-        // independent of the running values
-        const int code = (int)((quad_bcast_u32<pb>(sc4[jb >> 2]) >> (8 * (jb & 3))) & 0xFFu);
-        const double s = e4m3_f64(code);
-        const double wv = (double)__uint_as_float(quad_bcast_u32<pb>(__float_as_uint(wr[jb])));
-        const double gscale = s * halfS;     // E2M1(k) s S = (2 E2M1(k)) (s S / 2), all exact
-        double m[7];                          // the midpoints times s (exact: <= 7 significant bits)
+    for (int64_t ap = a0 - (int64_t)nprev * kTile; ap < a0; ap += kTile) {
+        double ev[4];                                  // this lane's errors: columns 16m + q of the tile
 #pragma unroll
-        for (int jm = 0; jm < 7; ++jm) m[jm] = e2m1_mid(jm) * s;
-        // the chain
-        const double xb = quad_bcast<pb>(x[jb]);
-        const float y = __fdiv_rn(__double2float_rn(xb), S);
-        const double ay = fabs((double)y);
-        // index of the nearest E2M1 value: the midpoints passed, a tie counting only toward an
-        // even index (midpoints 1, 3, 5); none for a zero scale
-        int k = 0;
+        for (int m = 0; m < 4; ++m) ev[m] = X[(ap + 16 * m + q) * rows + rc];
+        double t[16];
 #pragma unroll
-        for (int jm = 0; jm < 7; ++jm) k += ((jm & 1) ? ay >= m[jm] : ay > m[jm]) ? 1 : 0;
-        k = code == 0 ? 0 : k;
-        const bool neg = signbit(y);
-        const double wq = (double)((0xC8643210u >> (4 * k)) & 15u) * gscale;
-        const double e = wv - (neg ? -wq : wq);
-        // the quad's four lanes store the same code and error
-        crow[L.pc[b]] = (uint8_t)((neg ? 8 : 0) | k);
-        erow[b] = e;
+        for (int k = 0; k < 16; ++k) t[k] = Uc[(ap + (tid >> 6) + 4 * k) * n + a0 + (tid & 63)];   // by rows
+        __syncthreads();                               // the previous block is used
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            if (4 * j + 3 > b) {             // some lane of the quad holds a column past b
-                const double v = x[j] + e * Tp[b * kTRow + j];
-                x[j] = (4 * j > b || p > pb) ? v : x[j];
+        for (int k = 0; k < 16; ++k) L.T[(tid >> 6) + 4 * k][row16_slot(tid & 63)] = t[k];
+        __syncthreads();
+        double tc[4];
+        read_row(tc, Tp);
+        auto term = [&](auto bc) {
+            constexpr int b = decltype(bc)::value;
+            double tn[4];                              // the next row of U: read a step ahead, no further
+            read_row(tn, Tp + (b + 1 < kTile ? b + 1 : b) * kTRow);
+            __builtin_amdgcn_sched_barrier(0);
+            const double e = row_bcast<(b & 15)>(ev[b >> 4]);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                x[m] = x[m] + e * tc[m];
+                tc[m] = tn[m];
             }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        for_each_index(term, std::make_integer_sequence<int, kTile>());
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 16; ++k) L.T[tid & 63][row16_slot((tid >> 6) + 4 * k)] = own[k];   // own[k] = U_{b, a}: b = tid & 63
+    __syncthreads();
+    const float S = tensor_scale[0];
+    const float rS = __fdiv_rn(1.0f, S);
+    const int64_t nb = n / block;
+    ColumnScale cs[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const int c = L.pc[16 * m + q];
+        const int code = scales[rc * nb + c / block];
+        const double s = e4m3_f64(code);
+        const float sf = (float)s;
+        cs[m].w = (double)load_w<In>(w, rc * n + c);
+        cs[m].sS = s * (double)S;
+        cs[m].M = code == 0 ? 0.f : __uint_as_float((__float_as_uint(sf) & 0x007FFFFFu) | 0x3F800000u);
+        cs[m].rM = code == 0 ? 0.f : __fdiv_rn(1.0f, cs[m].M);
+        cs[m].cvs = code == 0 ? 1.0f : sf;
+        cs[m].code = code;
+    }
+    double xs[4], e[4];
+    uint32_t nib[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) xs[m] = x[m];
+    bool ok = S >= 0x1p-26f && S <= 0x1p26f;
+    double tc[4];
+    read_row(tc, Tp);
+    auto column = [&](auto bc) {
+        constexpr int b = decltype(bc)::value, qb = b & 15, mb = b >> 4;
+        double tn[4];
+        read_row(tn, Tp + (b + 1 < kTile ? b + 1 : b) * kTRow);
+        __builtin_amdgcn_sched_barrier(0);
+        quantize_fast(x[mb], S, rS, cs[mb], &e[mb], &nib[mb], &ok);
+        const double eb = row_bcast<qb>(e[mb]);
+#pragma unroll
+        for (int m = mb; m < 4; ++m) {
+            const double v = x[m] + eb * tc[m];
+            x[m] = m > mb || q > qb ? v : x[m];
         }
+#pragma unroll
+        for (int m = 0; m < 4; ++m) tc[m] = tn[m];
         __builtin_amdgcn_sched_barrier(0);
     };
     for_each_index(column, std::make_integer_sequence<int, kTile>());
-}
-
-template <typename In>
-__global__ __launch_bounds__(4 * kTile) void tile_kernel(const In* __restrict__ w, const int* __restrict__ perm,
-                                                         const double* __restrict__ Uc,
-                                                         const uint8_t* __restrict__ scales,
-                                                         const float* __restrict__ tensor_scale,
-                                                         int64_t rows, int64_t n, int block, int64_t a0,
-                                                         const double* __restrict__ X,
-                                                         double* __restrict__ Et,
-                                                         uint8_t* __restrict__ codes) {
-    __shared__ TileLds L;
-    tile_body<In>(w, perm, Uc, scales, tensor_scale, rows, n, block, a0, X, Et, codes, blockIdx.x, L);
-}
-
-// X[r][k] += sum over the tile's b (in order) of Et[r][b] * U_{a0+b, k}, for k in [kstart,
-// kend): one 16R x 16R output block (column block bx, row block by) per workgroup, R x R values
-// per lane, the terms staged 32 at a time (so that four workgroups of the 64 x 64 blocks fit a
-// CU's LDS: four waves per SIMD to issue the binary64 chains).  The 32 x 32 blocks (R = 2)
-// serve the next tile's columns, which are on the critical path.
-template <int R>
-struct alignas(16) QTrailLdsT {
-    double Es[kHalf][16 * R + 2];  // Es[b][row] (rows padded: 16-byte rows, staging writes spread)
-    double Us[kHalf][16 * R + 2];  // Us[b][col]
-};
-using QTrailLds = QTrailLdsT<4>;
-
-// Lane (tr, tc) owns rows r0 + R tr .. + R - 1 and columns k0 + R tc .. + R - 1, so that its X
-// values and its operands of a step sit in 16-byte pairs.  kstart, kend and the blocks' columns
-// are multiples of 32, so a lane's columns are all inside [kstart, kend) or all outside.
-template <int R>
-__device__ __forceinline__ void trailing_body(const double* __restrict__ Et, const double* __restrict__ Uc,
-                                              int64_t rows, int64_t n, int64_t a0, int64_t kstart,
-                                              int64_t kend, double* __restrict__ X, int64_t bx,
-                                              int64_t by, QTrailLdsT<R>& L) {
-    static_assert(R % 2 == 0, "pairs of values");
-    constexpr int B = 16 * R;
-    const int64_t r0 = by * B;
-    const int64_t k0 = kstart + bx * B;
-    const int tr = threadIdx.x / 16, tc = threadIdx.x % 16;      // 16 x 16 lanes, R x R each
-    const int64_t kc = k0 + R * tc;
-    const bool cols_in = kc < kend;
-    double acc[R][R];
+    if (__any(!ok)) {                                  // the wave's rows once more, by the definition
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-        const int64_t r = r0 + R * tr + i;
-        const double2* src = reinterpret_cast<const double2*>(X + r * n + kc);
+        for (int m = 0; m < 4; ++m) x[m] = xs[m];
 #pragma unroll
-        for (int j = 0; j < R; j += 2) {
-            const double2 v = (r < rows && cols_in) ? src[j / 2] : make_double2(0.0, 0.0);
-            acc[i][j] = v.x;
-            acc[i][j + 1] = v.y;
-        }
-    }
-    // each half's operands are loaded into registers while the previous half is computed
-    constexpr int kPer = B * kHalf / 256;
-    double pe[kPer], pu[kPer];
-    auto fetch = [&](int h) {
+        for (int mb = 0; mb < 4; ++mb)
+#pragma unroll 1
+            for (int qb = 0; qb < 16; ++qb) {
+                quantize_any(x[mb], S, cs[mb], &e[mb], &nib[mb]);
+                const double eb = lane_row_value(e[mb], qb);
 #pragma unroll
-        for (int e = 0; e < kPer; ++e) {
-            const int t = threadIdx.x + 256 * e, rr = t / kHalf, b = t % kHalf;   // coalesced over b
-            pe[e] = r0 + rr < rows ? Et[(r0 + rr) * kTile + h + b] : 0.0;
-            pu[e] = k0 + rr < kend ? Uc[(k0 + rr) * n + a0 + h + b] : 0.0;
-        }
-    };
-    fetch(0);
-    for (int h = 0; h < kTile; h += kHalf) {
-        __syncthreads();                                          // the previous half is used
-#pragma unroll
-        for (int e = 0; e < kPer; ++e) {
-            const int t = threadIdx.x + 256 * e, rr = t / kHalf, b = t % kHalf;
-            L.Es[b][rr] = pe[e];
-            L.Us[b][rr] = pu[e];
-        }
-        __syncthreads();
-        if (h + kHalf < kTile) fetch(h + kHalf);
-#pragma unroll(R == 2 ? 4 : 2)
-        for (int b = 0; b < kHalf; ++b) {
-            double e[R], u[R];
-            const double2* ep = reinterpret_cast<const double2*>(&L.Es[b][R * tr]);
-            const double2* up = reinterpret_cast<const double2*>(&L.Us[b][R * tc]);
-#pragma unroll
-            for (int i = 0; i < R; i += 2) {
-                const double2 ev = ep[i / 2], uv = up[i / 2];
-                e[i] = ev.x;
-                e[i + 1] = ev.y;
-                u[i] = uv.x;
-                u[i + 1] = uv.y;
+                for (int m = mb; m < 4; ++m) {
+                    const double v = x[m] + eb * Tp[(16 * mb + qb) * kTRow + m];
+                    x[m] = m > mb || q > qb ? v : x[m];
+                }
             }
-#pragma unroll
-            for (int i = 0; i < R; ++i)
-#pragma unroll
-                for (int j = 0; j < R; ++j) acc[i][j] = acc[i][j] + e[i] * u[j];
-        }
     }
+    if (live) {
 #pragma unroll
-    for (int i = 0; i < R; ++i) {
-        const int64_t r = r0 + R * tr + i;
-        if (r < rows && cols_in) {
-            double2* dst = reinterpret_cast<double2*>(X + r * n + kc);
-#pragma unroll
-            for (int j = 0; j < R; j += 2) dst[j / 2] = make_double2(acc[i][j], acc[i][j + 1]);
+        for (int m = 0; m < 4; ++m) {
+            X[(a0 + 16 * m + q) * rows + r] = e[m];    // the tile's errors take its values' place
+            codes[r * n + L.pc[16 * m + q]] = (uint8_t)nib[m];
         }
     }
 }
 
-template <int R>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void trailing_kernel(
-        const double* __restrict__ Et, const double* __restrict__ Uc, int64_t rows, int64_t n, int64_t a0,
-        int64_t kstart, int64_t kend, double* __restrict__ X) {
-    __shared__ QTrailLdsT<R> L;
-    trailing_body<R>(Et, Uc, rows, n, a0, kstart, kend, X, blockIdx.x, blockIdx.y, L);
-}
+// X[k][r] += sum over nterms errors b = a0, a0 + 1, ... in order of E[b][r] * U_{b, k}, for 128 rows (two
+// to a lane, 64 apart) and 8 columns k0 .. k0 + 7 of each wave.  E is read over consecutive rows;
+// U_{b, k..k+7} is the same for all lanes and comes through the scalar cache into scalar registers, an
+// operand of the binary64 instructions as it is: no LDS, no barrier, 32 arithmetic instructions for
+// two loads of a lane and one scalar load.  Scalar loads return out of order, so they are waited for
+// all at once, some 700 cycles after their issue: two steps' are fetched a pair of steps ahead (16
+// columns and one step ahead left a wave waiting for them, 300 ns a step).  Bound by binary64 issue:
+// a SIMD with four such waves takes 5.7 cycles an instruction (4.9 with eight, 12.5 with one; a
+// multiply and an addition each, as the definition rounds them), and the launches of [4096, 4096]
+// take 3.76 ms in all, of which the terms are 2.5.  (4 x 4 values per lane with both operands in
+// LDS, the tile's chain of 35 us beside them: 4.4 ms.)
+typedef double double8 __attribute__((ext_vector_type(8)));
+constexpr int kTermRows = 128, kTermCols = 8;
 
-// Look-ahead: the next tile (workgroups 0 .. ntile-1, its errors into Etn) beside the rest of
-// the current tile's trailing update, columns [kstart, n) with the current tile's errors Etc
-// (the other workgroups, ncb column blocks per row block).  The next tile's columns already
-// hold every earlier term; the two touch disjoint values.
+__device__ __forceinline__ void add_terms(const double* __restrict__ Uc, int64_t rows, int64_t n, int64_t a0,
+                                          int nterms, int64_t k0, int64_t r0, double* __restrict__ X) {
+    constexpr int H = kTermRows / 64;                  // rows of a lane
+    constexpr int kAhead = 4;                          // steps of E in flight
+    const int lane = threadIdx.x & 63;
+    int64_t rr[H], rc[H];
+    double acc[H][kTermCols];
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        rr[h] = r0 + lane + 64 * h;
+        rc[h] = rr[h] < rows ? rr[h] : rows - 1;
+#pragma unroll
+        for (int c = 0; c < kTermCols; ++c) acc[h][c] = X[(k0 + c) * rows + rc[h]];
+    }
+    const double* ep = X + a0 * rows;
+    const double* up = Uc + a0 * n + k0;
+    // the wave's lines of U, touched once so that the scalar loads find them in the XCD's L2
+    const double t0 = up[(int64_t)lane * n], t1 = up[(int64_t)(nterms - 64 + lane) * n];
+    double e[H][kAhead], en[H][kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+        for (int h = 0; h < H; ++h) e[h][i] = ep[(int64_t)i * rows + rc[h]];
+    asm volatile("" ::"v"(t0), "v"(t1) : "memory");
+    auto urow = [&](int b) { return *reinterpret_cast<const double8*>(up + (int64_t)b * n); };
+    double8 u0 = urow(0), u1 = urow(1);
+    for (int b0 = 0; b0 < nterms; b0 += kAhead) {      // nterms: a multiple of 64
+        const int bn = b0 + kAhead < nterms ? b0 + kAhead : b0;
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+            for (int h = 0; h < H; ++h) en[h][i] = ep[(int64_t)(bn + i) * rows + rc[h]];
+#pragma unroll
+        for (int i = 0; i < kAhead; i += 2) {
+            const int b2 = i + 2 < kAhead ? b0 + i + 2 : bn;
+            const double8 n0 = urow(b2), n1 = urow(b2 + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            double p[H][kTermCols];                    // all products, then all sums: no instruction waits
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+#pragma unroll
+                for (int c = 0; c < kTermCols; ++c)
+#pragma unroll
+                    for (int h = 0; h < H; ++h) p[h][c] = e[h][i + half] * (half ? u1[c] : u0[c]);
+#pragma unroll
+                for (int c = 0; c < kTermCols; ++c)
+#pragma unroll
+                    for (int h = 0; h < H; ++h) acc[h][c] = acc[h][c] + p[h][c];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            u0 = n0;
+            u1 = n1;
+        }
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+            for (int h = 0; h < H; ++h) e[h][i] = en[h][i];
+    }
+#pragma unroll
+    for (int c = 0; c < kTermCols; ++c)
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+            if (rr[h] < rows) X[(k0 + c) * rows + rr[h]] = acc[h][c];
+}
+// Launch t: tile t (workgroups 0 .. ntile-1; nprev tiles' terms first) beside the terms of nterms
+// errors from ap on ncb blocks of 32 columns from kstart (the other workgroups, 128 rows each).  While
+// many columns are left they are read and written once per pair of tiles: pair (2j-2, 2j-1) goes to
+// the columns past tile 2j in the launches 2j and 2j+1, half of them each, the first with tile 2j+1
+// among them, so tile 2j adds the pair's terms itself and tile 2j+1 only tile 2j's.  For the last
+// columns, where the tile's own chain is the longer role, every launch adds the tile before.
+// Every column has its terms in ascending order, and the two roles touch disjoint values.
 template <typename In>
-__global__ __launch_bounds__(4 * kTile) __attribute__((amdgpu_waves_per_eu(4))) void tile_lookahead_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void quantize_kernel(
         const In* __restrict__ w, const int* __restrict__ perm, const double* __restrict__ Uc,
         const uint8_t* __restrict__ scales, const float* __restrict__ tensor_scale, int64_t rows,
-        int64_t n, int block, int64_t a0n, double* __restrict__ X, double* __restrict__ Etn,
-        uint8_t* __restrict__ codes, int64_t ntile, const double* __restrict__ Etc, int64_t a0c,
-        int64_t kstart, int64_t ncb) {
-    __shared__ union {
-        TileLds t;
-        QTrailLds q;
-    } L;
+        int64_t n, int block, int64_t a0, int nprev, double* __restrict__ X, uint8_t* __restrict__ codes,
+        int64_t ntile, int64_t ap, int nterms, int64_t kstart, int64_t ncb) {
+    __shared__ TileLds L;
     if ((int64_t)blockIdx.x < ntile) {
-        tile_body<In>(w, perm, Uc, scales, tensor_scale, rows, n, block, a0n, X, Etn, codes, blockIdx.x,
-                      L.t);
+        tile_body<In>(w, perm, Uc, scales, tensor_scale, rows, n, block, a0, nprev, X, codes, blockIdx.x, L);
     } else {
         const int64_t idx = blockIdx.x - ntile;
-        trailing_body<4>(Etc, Uc, rows, n, a0c, kstart, n, X, idx % ncb, idx / ncb, L.q);
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        add_terms(Uc, rows, n, ap, nterms, kstart + (idx % ncb * 4 + wave) * kTermCols, idx / ncb * kTermRows, X);
     }
 }
 
@@ -686,7 +761,7 @@ __global__ void clear_status_kernel(int* status) { status[0] = 0; }
 // ---- workspace ---------------------------------------------------------------------------
 
 struct Layout {
-    size_t perm, diag, lambda, D, Uc, X, Et, codes, total;
+    size_t perm, inv, diag, lambda, D, Uc, X, codes, total;
 };
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -695,16 +770,21 @@ Layout layout_of(int64_t rows, int64_t n) {
     Layout l;
     size_t o = 0;
     l.perm = o;   o = align256(o + (size_t)n * sizeof(int));
+    l.inv = o;    o = align256(o + (size_t)n * sizeof(int));
     l.diag = o;   o = align256(o + (size_t)n * sizeof(double));
     l.lambda = o; o = align256(o + sizeof(double));
     l.D = o;      o = align256(o + (size_t)n * sizeof(double));
     l.Uc = o;     o = align256(o + (size_t)n * n * sizeof(double));
     l.X = o;      o = align256(o + (size_t)rows * n * sizeof(double));
-    l.Et = o;     o = align256(o + (size_t)2 * rows * kTile * sizeof(double));   // two tiles in turn
     l.codes = o;  o = align256(o + (size_t)rows * n);
     l.total = o;
     return l;
 }
+
+// The last tiles, whose terms go tile by tile: their launches are as long as a tile's own chain, and 64
+// terms are half the work of a wave beside it.  4, 16 and 28 of them: 3.94, 3.82, 3.87 ms for the
+// launches of [4096, 4096].
+constexpr int64_t kSingleTiles = 16;
 
 unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
@@ -715,17 +795,17 @@ int run_ldlq(const void* wv, int64_t rows, int64_t n, int block, const double* H
     const In* w = static_cast<const In*>(wv);
     const Layout l = layout_of(rows, n);
     int* perm = reinterpret_cast<int*>(ws + l.perm);
+    int* inv = reinterpret_cast<int*>(ws + l.inv);
     double* diag = reinterpret_cast<double*>(ws + l.diag);
     double* lambda = reinterpret_cast<double*>(ws + l.lambda);
     double* D = reinterpret_cast<double*>(ws + l.D);
     double* Uc = reinterpret_cast<double*>(ws + l.Uc);
     double* X = reinterpret_cast<double*>(ws + l.X);
-    double* Et = reinterpret_cast<double*>(ws + l.Et);
     uint8_t* codes = reinterpret_cast<uint8_t*>(ws + l.codes);
 
     hipLaunchKernelGGL(clear_status_kernel, dim3(1), dim3(1), 0, st, status);
     hipLaunchKernelGGL(diag_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, H, n, diag);
-    hipLaunchKernelGGL(order_kernel, dim3(blocks_for(n, 64)), dim3(64 * kOrderParts), 0, st, diag, n, perm);
+    hipLaunchKernelGGL(order_kernel, dim3(blocks_for(n, 64)), dim3(64 * kOrderParts), 0, st, diag, n, perm, inv);
     hipLaunchKernelGGL(damping_kernel, dim3(1), dim3(64), 0, st, diag, n, damp, lambda);
     if (hipGetLastError() != hipSuccess) return NVFP4_ERR_HIP;
     hipLaunchKernelGGL(init_a_kernel, dim3(blocks_for(n * n, 256)), dim3(256), 0, st, H, perm, lambda,
@@ -744,24 +824,30 @@ int run_ldlq(const void* wv, int64_t rows, int64_t n, int block, const double* H
                            n, k0, nb > 0 ? nb : 1, k0 - kTile, status);
         if (hipGetLastError() != hipSuccess) return NVFP4_ERR_HIP;
     }
-    hipLaunchKernelGGL(init_x_kernel<In>, dim3(blocks_for(rows * n, 256)), dim3(256), 0, st, w, perm,
-                       rows, n, X);
-    // quantize: tile 0, then per tile the next tile's columns, and then the next tile beside
-    // the rest of the trailing update (look-ahead); the tiles' errors alternate between two
-    // buffers
-    const unsigned rblocks = blocks_for(rows, kTile);
-    hipLaunchKernelGGL(tile_kernel<In>, dim3(rblocks), dim3(4 * kTile), 0, st, w, perm, Uc, scales, S,
-                       rows, n, block, (int64_t)0, X, Et, codes);
-    for (int64_t a0 = 0; a0 + kTile < n; a0 += kTile) {
-        double* Etc = Et + ((a0 / kTile) & 1) * rows * kTile;
-        double* Etn = Et + (((a0 / kTile) + 1) & 1) * rows * kTile;
-        hipLaunchKernelGGL(trailing_kernel<2>, dim3(2, blocks_for(rows, 32)), dim3(256), 0, st, Etc, Uc, rows,
-                           n, a0, a0 + kTile, a0 + 2 * kTile, X);
-        const int64_t rest = n - (a0 + 2 * kTile);                  // columns past the next tile
-        const int64_t ncb = (rest + kTile - 1) / kTile;
-        hipLaunchKernelGGL(tile_lookahead_kernel<In>, dim3((unsigned)(rblocks + ncb * rblocks)),
-                           dim3(4 * kTile), 0, st, w, perm, Uc, scales, S, rows, n, block, a0 + kTile, X, Etn,
-                           codes, (int64_t)rblocks, Etc, a0, a0 + 2 * kTile, ncb > 0 ? ncb : 1);
+    hipLaunchKernelGGL(init_x_kernel<In>, dim3((unsigned)(n / kTile), blocks_for(rows, kTile)), dim3(256), 0, st,
+                       w, inv, rows, n, X);
+    // quantize: tile t beside the terms of earlier tiles on the later columns (quantize_kernel)
+    const int64_t ntiles = n / kTile;
+    const unsigned tile_wgs = blocks_for(rows, kTileRows), row_wgs = blocks_for(rows, kTermRows);
+    const int64_t t0 = ntiles > kSingleTiles ? (ntiles - kSingleTiles) & ~(int64_t)1 : 0;   // the last pair's launch
+    for (int64_t t = 0; t < ntiles; ++t) {
+        const int64_t even = t & ~(int64_t)1;               // the launches even, even + 1 share a pair
+        const bool pairs = t < t0 || (t == t0 && t > 0);
+        int64_t c0 = t + 1, c1 = ntiles;                    // the tiles that receive terms
+        int nprev = t > 0 ? 1 : 0, nterms = nprev * kTile;
+        int64_t ap = (t - 1) * kTile;
+        if (pairs) {
+            const int64_t mid = t == t0 ? ntiles : even + 1 + (ntiles - even) / 2;
+            if (t == even) c1 = mid;
+            else c0 = mid;
+            ap = (even - 2) * kTile;
+            nterms = even >= 2 ? 2 * kTile : 0;
+            if (t == even && t >= 2) nprev = 2;
+        }
+        const int64_t ncb = nterms > 0 && c1 > c0 ? (c1 - c0) * (kTile / (4 * kTermCols)) : 0;
+        hipLaunchKernelGGL(quantize_kernel<In>, dim3((unsigned)(tile_wgs + ncb * row_wgs)), dim3(256), 0, st, w, perm,
+                           Uc, scales, S, rows, n, block, t * kTile, nprev, X, codes, (int64_t)tile_wgs, ap, nterms,
+                           c0 * kTile, ncb > 0 ? ncb : 1);
         if (hipGetLastError() != hipSuccess) return NVFP4_ERR_HIP;
     }
     hipLaunchKernelGGL(pack_kernel, dim3(blocks_for(rows * n / 2, 256)), dim3(256), 0, st, codes,

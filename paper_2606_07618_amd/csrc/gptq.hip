@@ -68,6 +68,15 @@ __device__ __forceinline__ double row_bcast(double v) {
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
+// Four consecutive values (16-byte aligned).
+__device__ __forceinline__ void read_row(double (&t)[4], const double* p) {
+    const double2 a = reinterpret_cast<const double2*>(p)[0], b = reinterpret_cast<const double2*>(p)[1];
+    t[0] = a.x;
+    t[1] = a.y;
+    t[2] = b.x;
+    t[3] = b.y;
+}
+
 // ---- column order and damping ------------------------------------------------------------
 
 __global__ __launch_bounds__(256) void diag_kernel(const double* __restrict__ H, int64_t n,
@@ -263,7 +272,7 @@ __global__ __launch_bounds__(4 * kTile) void factor_diag_kernel(double* __restri
 // row's columns j < kk loses (U_i,kk U_j,kk) D_kk.  So each value receives its terms kk = 63,
 // 62, ... in the order the column-by-column definition sums them.  A step holds no branch and
 // at most four updates per lane; the block's U and D are staged in LDS (each lane's columns of
-// a U row contiguous).
+// a U row contiguous) and read a step ahead: 13.2 -> 12.6 us a launch.
 constexpr int kPanelRows = 16;
 __device__ __forceinline__ int row16_slot(int j) { return 4 * (j & 15) + (j >> 4); }
 
@@ -289,19 +298,29 @@ __global__ __launch_bounds__(256) void factor_panel_kernel(double* __restrict__ 
     __syncthreads();
     if (i >= k0) return;                     // whole lane rows; rows share nothing
     const double* Up = &Ub[0][4 * q];
+    double dc = Db[kTile - 1], tc[4];
+    read_row(tc, Up + (kTile - 1) * kTile);
     auto step = [&](auto kc) {
         constexpr int kk = kTile - 1 - decltype(kc)::value, qk = kk & 15, mk = kk >> 4;
-        const double dk = Db[kk];
+        // the next step's row of U and D, read a step ahead
+        constexpr int kn = kk >= 1 ? kk - 1 : 0;
+        const double dk = dc;
+        double tn[4];
+        read_row(tn, Up + kn * kTile);
+        dc = Db[kn];
+        __builtin_amdgcn_sched_barrier(0);
         const double u = row_bcast<qk>(v[mk]) / dk;
         Uc[(k0 + kk) * n + i] = u;           // the row's lanes store the same value
         if (q == qk) uf[mk] = u;
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             if (16 * m < kk) {               // some lane of the row holds a column before kk
-                const double nv = v[m] - (u * Up[kk * kTile + m]) * dk;
+                const double nv = v[m] - (u * tc[m]) * dk;
                 v[m] = (16 * m + 15 < kk || q < kk - 16 * m) ? nv : v[m];
             }
+            tc[m] = tn[m];
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
     for_each_index(step, std::make_integer_sequence<int, kTile>());
     // the row's U once more by rows, in the lower triangle (nothing of A is there): the
@@ -520,14 +539,6 @@ __device__ __forceinline__ void quantize_fast(double x, float S, float rS, const
 
 __device__ __forceinline__ double lane_row_value(double v, int lane) {
     return __shfl(v, (int)(threadIdx.x & 48) | lane, 64);
-}
-
-__device__ __forceinline__ void read_row(double (&t)[4], const double* p) {
-    const double2 a = reinterpret_cast<const double2*>(p)[0], b = reinterpret_cast<const double2*>(p)[1];
-    t[0] = a.x;
-    t[1] = a.y;
-    t[2] = b.x;
-    t[3] = b.y;
 }
 
 template <typename In>

@@ -85,25 +85,37 @@ __global__ __launch_bounds__(256) void diag_kernel(const double* __restrict__ H,
     if (i < n) diag[i] = H[i * n + i];
 }
 
-// perm[rank(i)] = i, inv[i] = rank(i), rank = number of columns with a larger diagonal, or an equal one and a
-// smaller index (a stable descending order).  64 columns i per workgroup; each of its 16 waves
+// perm[rank(i)] = i, inv[i] = rank(i), rank = number of columns with a larger diagonal, or an equal one
+// and a smaller index (a stable descending order).  64 columns i per workgroup; each of its 16 waves
 // counts over a sixteenth of every 1024-value chunk of the diagonal staged in LDS (one value per
 // step, read by the wave's lanes alike), and the sixteen counts are added.
+// Beside them, the last workgroup: lambda = damp * (sum of the diagonal in index order) / n, one lane
+// adding the staged chunks.  At n = 4096 the sum is 31 us of dependent additions, the order 24 us.
 constexpr int kOrderParts = 16;
 __global__ __launch_bounds__(64 * kOrderParts) void order_kernel(const double* __restrict__ diag, int64_t n,
-                                                                 int* __restrict__ perm,
-                                                                 int* __restrict__ inv) {
+                                                                 int* __restrict__ perm, int* __restrict__ inv,
+                                                                 double damp, double* __restrict__ lambda) {
     constexpr int kChunk = 1024, kPer = kChunk / kOrderParts;
     __shared__ double chunk[kChunk];
     __shared__ int part_rank[kOrderParts][64];
+    const bool sum = blockIdx.x == gridDim.x - 1;
     const int il = threadIdx.x & 63, part = threadIdx.x >> 6;
     const int64_t i = (int64_t)blockIdx.x * 64 + il;
     const double d = i < n ? diag[i] : 0.0;
     int rank = 0;
+    double tr = 0.0;
     for (int64_t c0 = 0; c0 < n; c0 += kChunk) {
         __syncthreads();                                          // the previous chunk is used
         chunk[threadIdx.x] = c0 + threadIdx.x < n ? diag[c0 + threadIdx.x] : 0.0;
         __syncthreads();
+        if (sum) {
+            if (threadIdx.x == 0) {
+                const int m = (int)(n - c0 < kChunk ? n - c0 : kChunk);
+#pragma unroll 16
+                for (int k = 0; k < m; ++k) tr += chunk[k];
+            }
+            continue;
+        }
         const int64_t jb = c0 + part * kPer;
         const int m = (int)(n - jb < kPer ? (n - jb > 0 ? n - jb : 0) : kPer);
 #pragma unroll 8
@@ -111,6 +123,10 @@ __global__ __launch_bounds__(64 * kOrderParts) void order_kernel(const double* _
             const double e = chunk[part * kPer + jj];
             rank += (e > d || (e == d && jb + jj < i)) ? 1 : 0;
         }
+    }
+    if (sum) {
+        if (threadIdx.x == 0) lambda[0] = damp * (tr / (double)n);
+        return;
     }
     part_rank[part][il] = rank;
     __syncthreads();
@@ -122,42 +138,41 @@ __global__ __launch_bounds__(64 * kOrderParts) void order_kernel(const double* _
     }
 }
 
-// lambda = damp * (sum of the diagonal in index order) / n: one wave stages the diagonal in
-// chunks, one lane adds.
-__global__ __launch_bounds__(64) void damping_kernel(const double* __restrict__ diag, int64_t n, double damp,
-                                                     double* __restrict__ lambda) {
-    __shared__ double buf[1024];
-    double tr = 0.0;
-    for (int64_t c0 = 0; c0 < n; c0 += 1024) {
-        __syncthreads();
-        for (int t = threadIdx.x; t < 1024; t += 64) buf[t] = c0 + t < n ? diag[c0 + t] : 0.0;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const int m = (int)(n - c0 < 1024 ? n - c0 : 1024);
-#pragma unroll 16
-            for (int k = 0; k < m; ++k) tr += buf[k];
-        }
-    }
-    if (threadIdx.x == 0) lambda[0] = damp * (tr / (double)n);
-}
-
 // ---- factor: blocked, from the last 64-column block backwards ---------------------------
 // Uc holds A = Hp column-major (Uc[j n + i] = A_ij for i <= j; the lower triangle is never
 // written, and the values the kernels read from it feed only results they discard) and is
 // overwritten in place by U.  Element (i, j) must receive its terms k = n-1, n-2, ..., j+1 in that order; the blocks
 // are finished last-first and every kernel walks k downwards, so it does.
 
+// The damped, reordered Hessian, its upper triangle only (only that is read as A), 64 x 64 values per
+// workgroup through LDS: read along the rows of H (64 values scattered over one row of 8 n bytes),
+// written along the columns of Uc.  An XCD (workgroup index mod 8) takes the tiles of one row block
+// after another, so that the block's 64 rows of H come from memory once and then from its L2:
+// [4096, 4096] 157 -> 73 us (each value's line of H was fetched for it alone).
 __global__ __launch_bounds__(256) void init_a_kernel(const double* __restrict__ H,
                                                      const int* __restrict__ perm,
                                                      const double* __restrict__ lambda, int64_t n,
                                                      double* __restrict__ Uc) {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= n * n) return;
-    const int64_t j = t / n, i = t % n;
-    if (i > j) return;                       // only the upper triangle is ever read as A
-    double v = H[(int64_t)perm[i] * n + perm[j]];
-    if (i == j) v = v + lambda[0];
-    Uc[t] = v;
+    __shared__ double v[kTile][kTile + 1];
+    __shared__ int pr[kTile];
+    const int64_t tiles = n / kTile, seq = blockIdx.x / 8;
+    const int64_t ti = seq / tiles * 8 + blockIdx.x % 8, tj = seq % tiles;
+    if (ti > tj) return;                               // also past the last row block: tj < tiles
+    const int64_t i0 = ti * kTile, j0 = tj * kTile;
+    const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
+    if (part == 0) pr[lane] = perm[i0 + lane];
+    const int pc = perm[j0 + lane];
+    __syncthreads();
+#pragma unroll 8
+    for (int a = part; a < kTile; a += 4) v[a][lane] = H[(int64_t)pr[a] * n + pc];
+    __syncthreads();
+    const int64_t i = i0 + lane;
+    for (int b = part; b < kTile; b += 4) {
+        const int64_t j = j0 + b;
+        double x = v[lane][b];
+        if (i == j) x = x + lambda[0];
+        if (i <= j) Uc[j * n + i] = x;
+    }
 }
 
 // The diagonal block [k0, k0 + 64): its D and its U, column by column from the last.  The
@@ -816,10 +831,11 @@ int run_ldlq(const void* wv, int64_t rows, int64_t n, int block, const double* H
 
     hipLaunchKernelGGL(clear_status_kernel, dim3(1), dim3(1), 0, st, status);
     hipLaunchKernelGGL(diag_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, H, n, diag);
-    hipLaunchKernelGGL(order_kernel, dim3(blocks_for(n, 64)), dim3(64 * kOrderParts), 0, st, diag, n, perm, inv);
-    hipLaunchKernelGGL(damping_kernel, dim3(1), dim3(64), 0, st, diag, n, damp, lambda);
+    hipLaunchKernelGGL(order_kernel, dim3(blocks_for(n, 64) + 1), dim3(64 * kOrderParts), 0, st, diag, n, perm, inv,
+                       damp, lambda);
     if (hipGetLastError() != hipSuccess) return NVFP4_ERR_HIP;
-    hipLaunchKernelGGL(init_a_kernel, dim3(blocks_for(n * n, 256)), dim3(256), 0, st, H, perm, lambda,
+    const int64_t tiles = n / kTile;
+    hipLaunchKernelGGL(init_a_kernel, dim3((unsigned)((tiles + 7) / 8 * 8 * tiles)), dim3(256), 0, st, H, perm, lambda,
                        n, Uc);
     // factor, from the last block: its diagonal block, then per block the panel above it, the
     // column of tiles the next diagonal block and panel need, and then the next diagonal block

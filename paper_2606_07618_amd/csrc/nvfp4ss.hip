@@ -46,7 +46,7 @@
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kLaneElems = 16;
+constexpr int kLaneElems = 16, kNarrowElems = 4;
 
 enum Method { kAbsMax = 0, kFourSix = 1, kSweepMse = 2, kSweepWmse = 3, kWindowMse = 4, kWindowWmse = 5 };
 
@@ -208,10 +208,11 @@ struct Loader;
 
 template <>
 struct Loader<float> {
-    static __device__ __forceinline__ void load(const float* p, float (&v)[kLaneElems]) {
+    template <int E>
+    static __device__ __forceinline__ void load(const float* p, float (&v)[E]) {
         const float4* q = reinterpret_cast<const float4*>(p);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < E / 4; ++k) {
             const float4 t = q[k];
             v[4 * k] = t.x;
             v[4 * k + 1] = t.y;
@@ -223,6 +224,13 @@ struct Loader<float> {
 
 template <>
 struct Loader<uint16_t> {   // bfloat16 bit patterns; widening to binary32 is exact
+    static __device__ __forceinline__ void load(const uint16_t* p, float (&v)[kNarrowElems]) {
+        const uint2 t = *reinterpret_cast<const uint2*>(p);
+        v[0] = __uint_as_float(t.x << 16);
+        v[1] = __uint_as_float(t.x & 0xFFFF0000u);
+        v[2] = __uint_as_float(t.y << 16);
+        v[3] = __uint_as_float(t.y & 0xFFFF0000u);
+    }
     static __device__ __forceinline__ void load(const uint16_t* p, float (&v)[kLaneElems]) {
         const uint4* q = reinterpret_cast<const uint4*>(p);
 #pragma unroll
@@ -238,10 +246,11 @@ struct Loader<uint16_t> {   // bfloat16 bit patterns; widening to binary32 is ex
     }
 };
 
-__device__ __forceinline__ void load_weights(const float* p, float (&w)[kLaneElems]) {
+template <int E>
+__device__ __forceinline__ void load_weights(const float* p, float (&w)[E]) {
     const float4* q = reinterpret_cast<const float4*>(p);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < E / 4; ++k) {
         const float4 t = q[k];
         w[4 * k] = t.x;
         w[4 * k + 1] = t.y;
@@ -358,12 +367,12 @@ __device__ __forceinline__ uint32_t any_bits() {
 
 // u[i] ~ |y_i| / M (rounded once); the conversion divides by 2^E exactly and rounds to E2M1;
 // its decode gives g 2^E and e = |y| - (g 2^E) M is formed with one fused multiply-add.
-template <bool WEIGHTED>
-__device__ __forceinline__ float cand_loss(const float (&u)[kLaneElems], const float (&y)[kLaneElems],
-                                           const float (&w)[kLaneElems], float cvs, float M) {
+template <bool WEIGHTED, int E>
+__device__ __forceinline__ float cand_loss(const float (&u)[E], const float (&y)[E],
+                                           const float (&w)[E], float cvs, float M) {
     float acc0 = 0.f, acc1 = 0.f;
 #pragma unroll
-    for (int i = 0; i < kLaneElems; i += 2) {
+    for (int i = 0; i < E; i += 2) {
         const uint32_t p = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(any_bits(), u[i], u[i + 1], cvs, 0);
         const float2v g = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(p, cvs, 0);
         const float e0 = fmaf(-g.x, M, fabsf(y[i]));
@@ -385,9 +394,9 @@ __device__ __forceinline__ float cand_loss(const float (&u)[kLaneElems], const f
 // two quotients live instead of sixteen.  Each loss is the same binary32 operation sequence
 // as cand_loss (even and odd elements in two chains, added at the end), so the values are
 // bit-identical; a code past 126 has NaN in M and cvs and scores NaN as there.
-template <bool WEIGHTED, int LPB, int NC>
-__device__ __forceinline__ void significand_group_losses(const float (&y)[kLaneElems],
-                                                         const float (&w)[kLaneElems],
+template <bool WEIGHTED, int LPB, int NC, int E>
+__device__ __forceinline__ void significand_group_losses(const float (&y)[E],
+                                                         const float (&w)[E],
                                                          const Scale* tab, int cb, int d,
                                                          float (&J)[NC], int dmin = 0, int dlim = NC) {
     // members d + 8k below dmin or at dlim and above are left out (and keep their J)
@@ -404,7 +413,7 @@ __device__ __forceinline__ void significand_group_losses(const float (&y)[kLaneE
         acc1[k] = 0.f;
     }
 #pragma unroll
-    for (int i = 0; i < kLaneElems; i += 2) {
+    for (int i = 0; i < E; i += 2) {
         float u0 = fabsf(y[i]) * rM, u1 = fabsf(y[i + 1]) * rM;
         // not rematerializable: the compiler would otherwise recompute them per candidate
         asm volatile("" : "+v"(u0), "+v"(u1));
@@ -442,8 +451,8 @@ __device__ __forceinline__ void significand_group_losses(const float (&y)[kLaneE
 // wait states between them, and a conversion or decode may read a VALU result of the
 // previous instruction on gfx950.  (The weighted loss gains nothing from this order and
 // keeps the compiler's.)
-template <int LPB, int NC>
-__device__ __forceinline__ void significand_group_losses_sched(const float (&y)[kLaneElems],
+template <int LPB, int NC, int E>
+__device__ __forceinline__ void significand_group_losses_sched(const float (&y)[E],
                                                                const Scale* tab, int cb, int d,
                                                                float (&J)[NC]) {
     const float rM = tab[cb + d].rM;
@@ -453,7 +462,7 @@ __device__ __forceinline__ void significand_group_losses_sched(const float (&y)[
         const float s0 = tab[cb + d].cvs, s1 = tab[cb + d + 8].cvs;
         float a00 = 0.f, a01 = 0.f, a10 = 0.f, a11 = 0.f;   // [candidate][element parity]
 #pragma unroll
-        for (int i = 0; i < kLaneElems; i += 2) {
+        for (int i = 0; i < E; i += 2) {
             const float u0 = fabsf(y[i]) * rM, u1 = fabsf(y[i + 1]) * rM;
             uint32_t p0, p1;
             float2v g0, g1;
@@ -487,7 +496,7 @@ __device__ __forceinline__ void significand_group_losses_sched(const float (&y)[
         const float s0 = tab[cb + d].cvs;
         float a00 = 0.f, a01 = 0.f;
 #pragma unroll
-        for (int i = 0; i < kLaneElems; i += 2) {
+        for (int i = 0; i < E; i += 2) {
             const float u0 = fabsf(y[i]) * rM, u1 = fabsf(y[i + 1]) * rM;
             uint32_t p0;
             float2v g0;
@@ -776,15 +785,15 @@ __device__ __forceinline__ float div_by_significand(float v, float M, float rM) 
 
 // Exact block loss in binary64, summed in element order 0..n-1 across the block's lanes:
 // e = |y| - g s exactly, term = e * e (times the weight), J = J + term.
-template <bool WEIGHTED, int LPB>
-__device__ double exact_loss(const float (&y)[kLaneElems], const float (&w)[kLaneElems], const Scale& sc,
+template <bool WEIGHTED, int LPB, int E>
+__device__ double exact_loss(const float (&y)[E], const float (&w)[E], const Scale& sc,
                              int part, int group_base_lane) {
     double acc = 0.0;
 #pragma unroll 1
     for (int l = 0; l < LPB; ++l) {
         if (part == l) {
 #pragma unroll
-            for (int i = 0; i < kLaneElems; ++i) {
+            for (int i = 0; i < E; ++i) {
                 float a = fabsf(y[i]);
                 float wi = w[i];
                 // keeps the binary64 conversions of |y| and w inside this rarely taken path
@@ -809,11 +818,11 @@ __device__ double exact_loss(const float (&y)[kLaneElems], const float (&w)[kLan
 // element of the block identically: the exact E2M1 rounding of u = RN32(|y| / M) (the quotient
 // the emit uses) at both scales gives the same g 2^E for all n elements.  Then every term of the
 // loss, weighted or not, is the same for both codes, and so are the two sums.
-template <int LPB>
-__device__ bool same_reconstruction(const float (&y)[kLaneElems], const Scale& s0, const Scale& s1) {
+template <int LPB, int E>
+__device__ bool same_reconstruction(const float (&y)[E], const Scale& s0, const Scale& s1) {
     uint32_t differ = 0u;
 #pragma unroll
-    for (int i = 0; i < kLaneElems; i += 2) {
+    for (int i = 0; i < E; i += 2) {
         const float u0 = div_by_significand(fabsf(y[i]), s0.M, s0.rM);
         const float u1 = div_by_significand(fabsf(y[i + 1]), s0.M, s0.rM);
         const float2v g0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(
@@ -1003,8 +1012,8 @@ struct Window {
 // The window has 1..126 codes and may differ between the lanes of a wave, so the candidate
 // losses are not kept: a running minimum and second minimum of the keys decide the argmin and
 // whether the band re-scoring is needed, and that rare path scores the candidates again.
-template <bool WGT, int LPB>
-__device__ int choose_window(const float (&y)[kLaneElems], const float (&w)[kLaneElems], float ymax,
+template <bool WGT, int LPB, int E>
+__device__ int choose_window(const float (&y)[E], const float (&w)[E], float ymax,
                              const Scale* tab, const Params& p, int part, int group_base,
                              int std_lower, bool table2) {
     const int c0 = floor_code(ymax, 6.0f, 1.0f / 6.0f, tab);
@@ -1023,13 +1032,13 @@ __device__ int choose_window(const float (&y)[kLaneElems], const float (&w)[kLan
         best2 = min(best2, max(best1, key));
         best1 = min(best1, key);
     };
-    float u[kLaneElems];
+    float u[E];
     if (__all(lo >= 8)) {
         // normal codes only: lo + t, lo + t + 8, ... share the significand of lo + t
         for (int t = 0; t < 8 && __any(t < ncand); ++t) {
             const Scale st = tab[t < ncand ? lo + t : -kTabLo];        // -16: a NaN entry
 #pragma unroll
-            for (int i = 0; i < kLaneElems; ++i) u[i] = fabsf(y[i]) * st.rM;
+            for (int i = 0; i < E; ++i) u[i] = fabsf(y[i]) * st.rM;
             for (int j = t; __any(j < ncand); j += 8) {
                 const Scale sj = tab[j < ncand ? lo + j : -kTabLo];
                 take(group_sum<LPB>(cand_loss<WGT>(u, y, w, sj.cvs, sj.M)), j);
@@ -1039,7 +1048,7 @@ __device__ int choose_window(const float (&y)[kLaneElems], const float (&w)[kLan
         for (int j = 0; __any(j < ncand); ++j) {
             const Scale sj = tab[j < ncand ? lo + j : -kTabLo];
 #pragma unroll
-            for (int i = 0; i < kLaneElems; ++i) u[i] = fabsf(y[i]) * sj.rM;
+            for (int i = 0; i < E; ++i) u[i] = fabsf(y[i]) * sj.rM;
             take(group_sum<LPB>(cand_loss<WGT>(u, y, w, sj.cvs, sj.M)), j);
         }
     }
@@ -1054,7 +1063,7 @@ __device__ int choose_window(const float (&y)[kLaneElems], const float (&w)[kLan
             for (int j = 0; j < ncand; ++j) {
                 const Scale sj = tab[lo + j];
 #pragma unroll
-                for (int i = 0; i < kLaneElems; ++i) u[i] = fabsf(y[i]) * sj.rM;
+                for (int i = 0; i < E; ++i) u[i] = fabsf(y[i]) * sj.rM;
                 const float J = group_sum<LPB>(cand_loss<WGT>(u, y, w, sj.cvs, sj.M));
                 if (__uint_as_float(__float_as_uint(J) & 0xFFFFFF80u) <= bound) {
                     const double jd = exact_loss<WGT, LPB>(y, w, sj, part, group_base);
@@ -1132,12 +1141,13 @@ __device__ __forceinline__ void zero_scale_padding(uint8_t* __restrict__ scales,
 // SWZ: scales in 128 x 4 tiles (block 16), the grid's last workgroups for their padding.  A kernel of
 // its own: the padding's branch ahead of a tile's loads costs a row-major layer 0.7 % (batched MSE
 // 361.3 -> 364.0 us).
-template <int METHOD, typename In, int N, bool SWIGLU, bool SWZ>
+// E: elements of a lane, 16, or 4 on small grids (narrow_lanes).
+template <int METHOD, typename In, int N, bool SWIGLU, bool SWZ, int E>
 __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ x,
                                                          const float* __restrict__ colw,
                                                          uint8_t* __restrict__ q,
                                                          uint8_t* __restrict__ scales, Params p) {
-    constexpr int LPB = N / kLaneElems;
+    constexpr int LPB = N / E;
     constexpr bool WEIGHTED_OBJ = METHOD == kSweepWmse || METHOD == kFourSix || METHOD == kWindowWmse;
     __shared__ Scale tab_all[kTabSize];
     Scale* tab = tab_all + kTabLo;                 // tab[c] for codes c in -16..143
@@ -1162,14 +1172,14 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
     const int64_t blk_c = active ? blk : 0;   // inactive lanes run on block 0, store nothing
 
     // The tile's loads go out first; the table fill and the global-scale fold overlap them.
-    float y[kLaneElems];
+    float y[E];
     if constexpr (SWIGLU) {           // the tensor is the producer's output, formed here
         static_assert(N == 16, "fused producer at block 16");
         swiglu_lane(reinterpret_cast<const uint16_t*>(x) + blk_c * N, p.up + blk_c * N, y);
     } else {
-        Loader<In>::load(x + blk_c * N + part * kLaneElems, y);
+        Loader<In>::load(x + blk_c * N + part * E, y);
     }
-    float w[kLaneElems];
+    float w[E];
     const bool use_w = WEIGHTED_OBJ && colw != nullptr;
     uint32_t row = 0, kb = 0;         // the block's row and block column
     if (use_w || SWZ) {
@@ -1180,10 +1190,10 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
     uint32_t wblk = 0;
     if (use_w) {
         wblk = (p.wgroups > 1 ? weight_group(row, p) * p.bpr : 0u) + kb;
-        load_weights(colw + (int64_t)wblk * N + part * kLaneElems, w);
+        load_weights(colw + (int64_t)wblk * N + part * E, w);
     } else {
 #pragma unroll
-        for (int i = 0; i < kLaneElems; ++i) w[i] = 1.0f;
+        for (int i = 0; i < E; ++i) w[i] = 1.0f;
     }
     fill_scale_table<METHOD == kAbsMax || METHOD == kFourSix>(tab_all);
     if (p.nx_per > 0) raise_next_slot(p, tile, next_share_max<In>(p, tile));   // uniform
@@ -1220,7 +1230,7 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
     {
     // ---- normalize y = RN32(x / S) -----------------------------------------------------
 #pragma unroll
-    for (int i = 0; i < kLaneElems; ++i) {
+    for (int i = 0; i < E; ++i) {
         const float xv = y[i];
         if (fast_div && fabsf(xv) >= 0x1p-74f) {
             y[i] = div_by_significand(xv, S, rS);    // exact for these ranges (Markstein)
@@ -1230,7 +1240,7 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
     }
     float ymax = 0.f;
 #pragma unroll
-    for (int i = 0; i < kLaneElems; i += 2) ymax = max3_abs(y[i], y[i + 1], ymax);
+    for (int i = 0; i < E; i += 2) ymax = max3_abs(y[i], y[i + 1], ymax);
     ymax = group_max<LPB>(ymax);
 
     // ---- choose the block scale code ---------------------------------------------------
@@ -1241,14 +1251,14 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
     } else if (METHOD == kFourSix) {
         const int c6 = nearest_code(ymax, 6.0f, floor_code(ymax, 6.0f, 1.0f / 6.0f, tab), tab);
         const int c4 = nearest_code(ymax, 4.0f, floor_code(ymax, 4.0f, 0.25f, tab), tab);
-        float u[kLaneElems];
+        float u[E];
         const Scale s6 = tab[c6], s4 = tab[c4];
 #pragma unroll
-        for (int i = 0; i < kLaneElems; ++i) u[i] = fabsf(y[i]) * s6.rM;
+        for (int i = 0; i < E; ++i) u[i] = fabsf(y[i]) * s6.rM;
         float j6 = group_sum<LPB>(use_w ? cand_loss<true>(u, y, w, s6.cvs, s6.M)
                                         : cand_loss<false>(u, y, w, s6.cvs, s6.M));
 #pragma unroll
-        for (int i = 0; i < kLaneElems; ++i) u[i] = fabsf(y[i]) * s4.rM;
+        for (int i = 0; i < E; ++i) u[i] = fabsf(y[i]) * s4.rM;
         float j4 = group_sum<LPB>(use_w ? cand_loss<true>(u, y, w, s4.cvs, s4.M)
                                         : cand_loss<false>(u, y, w, s4.cvs, s4.M));
         code = j4 < j6 ? c4 : c6;
@@ -1283,9 +1293,9 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
 #pragma unroll
                 for (int d = 0; d < NC; ++d) {
                     const Scale sd = tab[cb + d];
-                    float u[kLaneElems];
+                    float u[E];
 #pragma unroll
-                    for (int i = 0; i < kLaneElems; ++i) u[i] = fabsf(y[i]) * sd.rM;
+                    for (int i = 0; i < E; ++i) u[i] = fabsf(y[i]) * sd.rM;
                     J[d] = group_sum<LPB>(cand_loss<WGT>(u, y, w, sd.cvs, sd.M));
                 }
             }
@@ -1335,9 +1345,9 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
                 const float e = ymax - 6.0f * e4m3_value(cb + d);   // 6 s is exact
                 if (__any(active && !(e * e > thr))) {
                     const Scale sd = tab[cb + d];
-                    float u[kLaneElems];
+                    float u[E];
 #pragma unroll
-                    for (int i = 0; i < kLaneElems; ++i) u[i] = fabsf(y[i]) * sd.rM;
+                    for (int i = 0; i < E; ++i) u[i] = fabsf(y[i]) * sd.rM;
                     J[d] = group_sum<LPB>(cand_loss<false>(u, y, w, sd.cvs, sd.M));
                     jb = fminf(jb, J[d]);
                 } else {
@@ -1356,9 +1366,9 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
 #pragma unroll
             for (int d = 0; d < NC; ++d) {
                 const Scale sd = tab[cb + d];
-                float u[kLaneElems];
+                float u[E];
 #pragma unroll
-                for (int i = 0; i < kLaneElems; ++i) u[i] = fabsf(y[i]) * sd.rM;
+                for (int i = 0; i < E; ++i) u[i] = fabsf(y[i]) * sd.rM;
                 J[d] = group_sum<LPB>(cand_loss<WGT>(u, y, w, sd.cvs, sd.M));
             }
         }
@@ -1399,12 +1409,12 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
                     int db = -1;
                     // the weights again, from memory: this rare path keeps no registers
                     // occupied across the sweep
-                    float wx[kLaneElems];
+                    float wx[E];
                     if (WGT) {
-                        load_weights(colw + (int64_t)wblk * N + part * kLaneElems, wx);
+                        load_weights(colw + (int64_t)wblk * N + part * E, wx);
                     } else {
 #pragma unroll
-                        for (int i = 0; i < kLaneElems; ++i) wx[i] = 1.0f;
+                        for (int i = 0; i < E; ++i) wx[i] = 1.0f;
                     }
 #pragma unroll 1
                     for (int d = 0; d < NC; ++d) {
@@ -1426,29 +1436,36 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
 
     // ---- emit: exact FP4 codes at the chosen scale, packed two per byte ------------------
     const Scale sc = tab[code];
-    uint32_t packed[2] = {0u, 0u};
+    constexpr int kWords = (E + 7) / 8, kPer = E < 8 ? E : 8;
+    uint32_t packed[kWords];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        float u[8];
+    for (int h = 0; h < kWords; ++h) {
+        float u[kPer];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < kPer; ++i) {
             u[i] = div_by_significand(y[8 * h + i], sc.M, sc.rM);
         }
         uint32_t r = 0u;
         r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, u[0], u[1], sc.cvs, 0);
         r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, u[2], u[3], sc.cvs, 1);
-        r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, u[4], u[5], sc.cvs, 2);
-        r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, u[6], u[7], sc.cvs, 3);
+        if constexpr (kPer == 8) {
+            r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, u[4], u[5], sc.cvs, 2);
+            r = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(r, u[6], u[7], sc.cvs, 3);
+        }
         packed[h] = r;
     }
     if (active) {
-        uint2* dst = reinterpret_cast<uint2*>(q + ((blk * N + part * kLaneElems) >> 1));
-        // streamed past the caches (nothing here reads them again): 2-5 % for the
-        // bandwidth-bound AbsMax and 4/6 launches
-        u32x2 pv;
-        pv.x = packed[0];
-        pv.y = packed[1];
-        __builtin_nontemporal_store(pv, reinterpret_cast<u32x2*>(dst));
+        uint8_t* dst = q + ((blk * N + part * E) >> 1);
+        if constexpr (E == kNarrowElems) {
+            *reinterpret_cast<uint16_t*>(dst) = (uint16_t)packed[0];
+        } else {
+            // streamed past the caches (nothing here reads them again): 2-5 % for the
+            // bandwidth-bound AbsMax and 4/6 launches
+            u32x2 pv;
+            pv.x = packed[0];
+            pv.y = packed[kWords - 1];
+            __builtin_nontemporal_store(pv, reinterpret_cast<u32x2*>(dst));
+        }
         if (part == 0) {
             if (SWZ)             // through L2, which merges the 4-byte pieces of a tile's lines
                 scales[swizzled_offset(row, kb, p.sw_kt)] = (uint8_t)code;
@@ -1551,6 +1568,7 @@ struct Call {
     int layout = NVFP4_SCALES_ROW_MAJOR;          // online calls only
     int64_t wgroups = 1, wgroup_rows = 1;
     const void* up = nullptr;                     // fused SwiGLU calls: x is the gate
+    bool narrow = false;                          // 4 elements a lane (narrow_lanes)
 };
 
 // Workgroups of the quantization kernel: one lane per 16 elements, one workgroup per tile.
@@ -1559,23 +1577,41 @@ int64_t quant_grid(const Call& c) {
     return (lanes + kThreads - 1) / kThreads;
 }
 
+// Grids of at most this many workgroups of 16 elements a lane take 4 a lane instead, four lanes to a
+// block of 16: a wave that is alone on its SIMD issues an instruction in about 8 cycles, so a lane's
+// elements are the call's length until the SIMDs hold several waves.  Measured, 16 against 4 a lane
+// (bfloat16, swizzled scales): MSE on [1, 4096] 4.95 / 3.54 us, 64 workgroups 6.89 / 5.68, 256 of them
+// 7.39 / 6.92 (binary32 7.71 / 8.44), 512 8.12 / 9.08; AbsMax 2.93 / 2.63, 3.09 / 2.69, 3.22 / 3.10,
+// 3.44 / 3.82; four-over-six on 64 4.60 / 4.48, on 256 4.71 / 4.87.
+constexpr int64_t kNarrowTiles = 128;
+
+bool narrow_lanes(const Call& c, bool next_tensor) {
+    return c.block == 16 && c.method <= kSweepMse && !c.up && !next_tensor && quant_grid(c) <= kNarrowTiles;
+}
+
+template <int METHOD, typename In, int N, bool SWIGLU, bool SWZ, int E>
+hipError_t launch_grid(const Call& c, const Params& p) {
+    // bytes of a swizzled scale buffer that no block owns, one per lane
+    const uint64_t pad = SWZ ? (uint64_t)p.pad_mp * 4u * p.sw_kt - (uint64_t)p.rows * p.bpr : 0;
+    const int64_t grid = (int64_t)p.tiles + (int64_t)((pad + kThreads - 1) / kThreads);
+    hipLaunchKernelGGL((quant_kernel<METHOD, In, N, SWIGLU, SWZ, E>), dim3((unsigned)grid), dim3(kThreads), 0,
+                       c.stream, static_cast<const In*>(c.x), c.colw, c.q, c.scales, p);
+    return hipGetLastError();
+}
+
 template <int METHOD, typename In, int N, bool SWIGLU = false>
 hipError_t launch_quant(const Call& c, const Params& p) {
-    const In* x = static_cast<const In*>(c.x);
     if (c.layout == NVFP4_SCALES_SWIZZLED) {           // block 16 only
         if constexpr (N == 16 && METHOD <= kSweepWmse) {
-            // bytes of the scale buffer that no block owns, one per lane
-            const uint64_t pad = (uint64_t)p.pad_mp * 4u * p.sw_kt - (uint64_t)p.rows * p.bpr;
-            const int64_t grid = (int64_t)p.tiles + (int64_t)((pad + kThreads - 1) / kThreads);
-            hipLaunchKernelGGL((quant_kernel<METHOD, In, N, SWIGLU, true>), dim3((unsigned)grid),
-                               dim3(kThreads), 0, c.stream, x, c.colw, c.q, c.scales, p);
-            return hipGetLastError();
+            if constexpr (METHOD <= kSweepMse && !SWIGLU)
+                if (c.narrow) return launch_grid<METHOD, In, N, SWIGLU, true, kNarrowElems>(c, p);
+            return launch_grid<METHOD, In, N, SWIGLU, true, kLaneElems>(c, p);
         }
         return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL((quant_kernel<METHOD, In, N, SWIGLU, false>), dim3(p.tiles), dim3(kThreads), 0,
-                       c.stream, x, c.colw, c.q, c.scales, p);
-    return hipGetLastError();
+    if constexpr (N == 16 && METHOD <= kSweepMse && !SWIGLU)
+        if (c.narrow) return launch_grid<METHOD, In, N, SWIGLU, false, kNarrowElems>(c, p);
+    return launch_grid<METHOD, In, N, SWIGLU, false, kLaneElems>(c, p);
 }
 
 template <int METHOD, typename In>
@@ -1673,7 +1709,9 @@ hipError_t launch_main(const Call& c, hipStream_t stream, const Chain& chain = C
     p.tensor_scale = c.tensor_scale;
     p.nx = static_cast<const uint4*>(chain.nx);
     p.nx_vec = chain.nx ? chain.nx_bytes / 16 : 0;
-    const int64_t tiles = quant_grid(c);
+    const bool narrow = narrow_lanes(c, chain.nx != nullptr);
+    const int64_t lane_elems = narrow ? kNarrowElems : kLaneElems;
+    const int64_t tiles = (c.rows * c.cols / lane_elems + kThreads - 1) / kThreads;
     p.nx_per = p.nx_vec > 0 ? (p.nx_vec + tiles - 1) / tiles : 0;
     p.nx_slots = chain.nx_ws ? chain.nx_ws + kSlotWord0 : nullptr;
     p.sw_kt = (uint32_t)((c.cols / c.block + 3) / 4);
@@ -1689,6 +1727,7 @@ hipError_t launch_main(const Call& c, hipStream_t stream, const Chain& chain = C
     p.up = static_cast<const uint16_t*>(c.up);
     Call cs = c;
     cs.stream = stream;
+    cs.narrow = narrow;
     if (c.up) {                       // fused SwiGLU producer: bfloat16, block 16
         switch (c.method) {
             case kAbsMax: return launch_quant<kAbsMax, uint16_t, 16, true>(cs, p);

@@ -55,3 +55,24 @@ def test_dynamic_scale_on_both_folds(rows, cols, dtype, at):
     assert torch.equal(q, q2) and torch.equal(sc, sc2)
     zero_q, zero_sc, zero_S = nv.quantize(torch.zeros_like(x), "scalesweep_mse", 16)
     assert zero_S.item() == 1.0 and int(zero_q.max()) == 0
+
+
+# 1, 2, 127 and 128 workgroups of 16 elements a lane (4 a lane there), and 129, with ragged last ones
+@pytest.mark.parametrize("rows,cols", [(1, 16), (1, 4112), (127, 4096), (128, 4096), (129, 4096), (513, 1008)])
+@pytest.mark.parametrize("method", ["absmax", "four_over_six", "scalesweep_mse"])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_four_elements_a_lane(rows, cols, method, dtype):
+    import paper_2606_07618_amd as nv
+    g = workloads.generator(DEV, 73, rows, cols)
+    x = workloads.llm_weight(rows, cols, g, DEV, scale=1.0, outlier_frac=0.02).to(dtype)
+    x[0, :16] = 0.0
+    x[-1, -16:] = torch.tensor([6.0, 3.0, 1.5, 0.75] * 4, device=DEV).to(dtype)     # equal losses of two codes
+    imp = workloads.column_importance(cols, g, DEV, tokens=64) if method == "four_over_six" else None
+    q, sc, S = nv.quantize(x, method, 16, weight=imp)
+    torch.cuda.synchronize()
+    D = 448.0 if method == "absmax" else 256.0
+    S_ref, q_ref, sc_ref = oracle.quantize(method, workloads.host_array(x), 16, D, 0.0,
+                                           None if imp is None else imp.cpu().numpy())
+    assert S.item() == S_ref
+    assert np.array_equal(sc.cpu().numpy(), sc_ref)
+    assert np.array_equal(q.cpu().numpy(), q_ref)

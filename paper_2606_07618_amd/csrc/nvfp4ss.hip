@@ -53,7 +53,8 @@ enum Method { kAbsMax = 0, kFourSix = 1, kSweepMse = 2, kSweepWmse = 3, kWindowM
 // Workspace words: one |x|-maximum bit pattern per workgroup of the reduction pass, then S
 // and 1/S; from word kSlotWord0 on, 64 |x|-maximum slots, each on its own 128-byte line,
 // which the workgroups of the quantization kernel of the preceding tensor of a batched call
-// raise atomically (slot = workgroup index mod 64).  Atomics on one line serialize (about
+// raise atomically (slot = workgroup index mod 64; on a small grid the reduction pass leaves its
+// partials there instead, four to a slot).  Atomics on one line serialize (about
 // 11 ns apiece measured on MI355X, i.e. 160 us for one per workgroup of a 14336-workgroup
 // grid); spread over 64 lines they cost nothing measurable.
 constexpr int kMaxPartials = 256;

@@ -140,6 +140,69 @@ __global__ __launch_bounds__(kLanes) void norms_partial_kernel(const In* __restr
             part[((int64_t)blockIdx.y * gout + g) * cols + c] = acc_g[g][lane];
 }
 
+template <typename In>
+__device__ __forceinline__ float load_value(const In* x, int64_t i);
+
+template <>
+__device__ __forceinline__ float load_value<float>(const float* x, int64_t i) { return x[i]; }
+
+template <>
+__device__ __forceinline__ float load_value<uint16_t>(const uint16_t* x, int64_t i) {
+    return __uint_as_float((uint32_t)x[i] << 16);
+}
+
+// The same sums straight from memory, for long runs on a grid that fills the chip several times over: no
+// tile in LDS, so twice the waves of a CU, and a run's additions wait for no second pass through LDS.
+// K [16, 8, 4096, 128] bfloat16 41.9 us a call against 44.7 through tiles; Q-like [1048576, 128]
+// binary32 114 against 118.  With short runs or few waves the tiles are the faster form ([14336,
+// 4096], runs of one row: 26.7 against 130).
+template <typename In>
+__global__ __launch_bounds__(kLanes) void norms_runs_kernel(const In* __restrict__ x, int64_t rows,
+                                                            int64_t cols, int64_t group_rows,
+                                                            int64_t groups, int64_t group_div, int gout,
+                                                            int64_t chunk_rows, double* __restrict__ part) {
+    extern __shared__ double acc_lds[];          // [gout][64]: sized at launch
+    double (*acc_g)[kLanes] = reinterpret_cast<double (*)[kLanes]>(acc_lds);
+    const int lane = threadIdx.x;
+    const int64_t c = (int64_t)blockIdx.x * kLanes + lane;
+    const int64_t r0 = (int64_t)blockIdx.y * chunk_rows;
+    const int64_t r1 = r0 + chunk_rows < rows ? r0 + chunk_rows : rows;
+    for (int g = 0; g < gout; ++g) acc_g[g][lane] = 0.0;
+    // rows are walked in runs of one group: r = q * group_rows + rem, and q mod groups =
+    // gd * group_div + gm, so a run ends after (group_div - gm) * group_rows - rem rows
+    int64_t rem = r0 % group_rows;
+    const int64_t gi = (r0 / group_rows) % groups;
+    int64_t gm = gi % group_div;
+    int gd = (int)(gi / group_div);
+    const bool col_ok = c < cols;
+    const In* xc = x + (col_ok ? c : 0);
+    for (int64_t r = r0; r < r1;) {
+        const int64_t run = (group_div - gm) * group_rows - rem;
+        const int64_t end = r + run < r1 ? r + run : r1;
+        double acc = 0.0;
+        int64_t rr = r;
+        for (; rr + 8 <= end; rr += 8) {          // eight independent loads in flight
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = load_value<In>(xc, (rr + j) * cols);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc += (double)v[j] * (double)v[j];
+        }
+        for (; rr < end; ++rr) {
+            const double v = (double)load_value<In>(xc, rr * cols);
+            acc += v * v;
+        }
+        if (col_ok) acc_g[gd][lane] += acc;
+        r = end;
+        rem = 0;
+        gm = 0;
+        gd = gd + 1 == gout ? 0 : gd + 1;
+    }
+    if (c < cols)
+        for (int g = 0; g < gout; ++g)
+            part[((int64_t)blockIdx.y * gout + g) * cols + c] = acc_g[g][lane];
+}
+
 // One workgroup per (group, 64 columns): 16 waves each add a contiguous sixteenth of the chunk
 // partials in order (eight loads in flight), then the sixteen sums are added in order.
 constexpr int kFinalSubs = 16;
@@ -223,7 +286,13 @@ int nvfp4_channel_sq_norms(const void* x, int dtype, int64_t rows, int64_t cols,
                            (int)gout, cr, part);
     };
     const bool wide = ((uintptr_t)x & 15) == 0 && cols * (dtype == NVFP4_IN_F32 ? 4 : 2) % 16 == 0;
-    if (rows > 0 && dtype == NVFP4_IN_F32)
+    // runs of at least a smallest chunk, and 16 waves for each of the 256 CUs
+    const bool runs = gout > 1 && group_div * group_rows >= kMinChunkRows && (int64_t)grid.x * grid.y >= 4096;
+    if (rows > 0 && runs && dtype == NVFP4_IN_F32)
+        launch(norms_runs_kernel<float>, static_cast<const float*>(x));
+    else if (rows > 0 && runs)
+        launch(norms_runs_kernel<uint16_t>, static_cast<const uint16_t*>(x));
+    else if (rows > 0 && dtype == NVFP4_IN_F32)
         launch(wide ? norms_partial_kernel<float, true> : norms_partial_kernel<float, false>,
                static_cast<const float*>(x));
     else if (rows > 0)

@@ -35,3 +35,18 @@ def test_norms_edges(rows, cols, args, dtype):
     # at most 700 additions of rounding 2^-53 each, then one rounding to binary32 (2^-24)
     assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= ref * (2.0 ** -24 + 700 * 2.0 ** -53))
     assert torch.equal(got.view(torch.int32), shifted.view(torch.int32))    # one order of additions
+
+
+# runs of at least 256 rows on 4096 workgroups (straight from memory), and one chunk fewer (tiles): 2048
+# chunks of 256 rows and 2 column tiles, with a ragged last run and last columns
+@pytest.mark.parametrize("rows", [2048 * 256, 2048 * 256 - 5, 2047 * 256])
+@pytest.mark.parametrize("args", [(256, 3, 1, 1), (1000, 4, 2, 2)])
+def test_norms_long_runs(rows, args):
+    import paper_2606_07618_amd as nv
+    g = workloads.generator(DEV, 92, rows)
+    x = torch.randn((rows, 72), generator=g, device=DEV).to(torch.bfloat16)
+    got = nv.channel_sq_norms(x, *args)
+    torch.cuda.synchronize()
+    ref = reference(x, *args)
+    # at most 2^19 additions of rounding 2^-53 each on either side, then one rounding to binary32
+    assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= ref * (2.0 ** -24 + 2.0 ** -33))

@@ -787,7 +787,7 @@ __global__ void clear_status_kernel(int* status) { status[0] = 0; }
 // ---- workspace ---------------------------------------------------------------------------
 
 struct Layout {
-    size_t perm, inv, diag, lambda, D, Uc, X, codes, total;
+    size_t perm, diag, lambda, D, Uc, X, codes, total;
 };
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -796,12 +796,13 @@ Layout layout_of(int64_t rows, int64_t n) {
     Layout l;
     size_t o = 0;
     l.perm = o;   o = align256(o + (size_t)n * sizeof(int));
-    l.inv = o;    o = align256(o + (size_t)n * sizeof(int));
     l.diag = o;   o = align256(o + (size_t)n * sizeof(double));
     l.lambda = o; o = align256(o + sizeof(double));
     l.D = o;      o = align256(o + (size_t)n * sizeof(double));
     l.Uc = o;     o = align256(o + (size_t)n * n * sizeof(double));
     l.X = o;      o = align256(o + (size_t)rows * n * sizeof(double));
+    // unused room of 128 values a row: the size that callers reserve stays what it has been
+    o = align256(o + (size_t)2 * rows * kTile * sizeof(double));
     l.codes = o;  o = align256(o + (size_t)rows * n);
     l.total = o;
     return l;
@@ -821,7 +822,7 @@ int run_ldlq(const void* wv, int64_t rows, int64_t n, int block, const double* H
     const In* w = static_cast<const In*>(wv);
     const Layout l = layout_of(rows, n);
     int* perm = reinterpret_cast<int*>(ws + l.perm);
-    int* inv = reinterpret_cast<int*>(ws + l.inv);
+    int* inv = reinterpret_cast<int*>(ws + l.D);        // read before the factor writes D
     double* diag = reinterpret_cast<double*>(ws + l.diag);
     double* lambda = reinterpret_cast<double*>(ws + l.lambda);
     double* D = reinterpret_cast<double*>(ws + l.D);
@@ -837,6 +838,8 @@ int run_ldlq(const void* wv, int64_t rows, int64_t n, int block, const double* H
     const int64_t tiles = n / kTile;
     hipLaunchKernelGGL(init_a_kernel, dim3((unsigned)((tiles + 7) / 8 * 8 * tiles)), dim3(256), 0, st, H, perm, lambda,
                        n, Uc);
+    hipLaunchKernelGGL(init_x_kernel<In>, dim3((unsigned)(n / kTile), blocks_for(rows, kTile)), dim3(256), 0, st,
+                       w, inv, rows, n, X);
     // factor, from the last block: its diagonal block, then per block the panel above it, the
     // column of tiles the next diagonal block and panel need, and then the next diagonal block
     // beside the rest of the trailing update (look-ahead)
@@ -851,8 +854,6 @@ int run_ldlq(const void* wv, int64_t rows, int64_t n, int block, const double* H
                            n, k0, nb > 0 ? nb : 1, k0 - kTile, status);
         if (hipGetLastError() != hipSuccess) return NVFP4_ERR_HIP;
     }
-    hipLaunchKernelGGL(init_x_kernel<In>, dim3((unsigned)(n / kTile), blocks_for(rows, kTile)), dim3(256), 0, st,
-                       w, inv, rows, n, X);
     // quantize: tile t beside the terms of earlier tiles on the later columns (quantize_kernel)
     const int64_t ntiles = n / kTile;
     const unsigned tile_wgs = blocks_for(rows, kTileRows), row_wgs = blocks_for(rows, kTermRows);

@@ -86,7 +86,9 @@ __global__ __launch_bounds__(256) void diag_kernel(const double* __restrict__ H,
 }
 
 // perm[rank(i)] = i, inv[i] = rank(i), rank = number of columns with a larger diagonal, or an equal one
-// and a smaller index (a stable descending order).  64 columns i per workgroup; each of its 16 waves
+// and a smaller index (a stable descending order).  A NaN counts as -infinity: it would compare false with
+// every value and share a rank, and a rank that no column has leaves perm unwritten there, an index out of
+// range.  (The sum keeps it, so the factor reports it.)  64 columns i per workgroup; each of its 16 waves
 // counts over a sixteenth of every 1024-value chunk of the diagonal staged in LDS (one value per
 // step, read by the wave's lanes alike), and the sixteen counts are added.
 // Beside them, the last workgroup: lambda = damp * (sum of the diagonal in index order) / n, one lane
@@ -101,12 +103,14 @@ __global__ __launch_bounds__(64 * kOrderParts) void order_kernel(const double* _
     const bool sum = blockIdx.x == gridDim.x - 1;
     const int il = threadIdx.x & 63, part = threadIdx.x >> 6;
     const int64_t i = (int64_t)blockIdx.x * 64 + il;
-    const double d = i < n ? diag[i] : 0.0;
+    auto order_key = [](double v) { return v == v ? v : -(double)INFINITY; };
+    const double d = i < n ? order_key(diag[i]) : 0.0;
     int rank = 0;
     double tr = 0.0;
     for (int64_t c0 = 0; c0 < n; c0 += kChunk) {
         __syncthreads();                                          // the previous chunk is used
-        chunk[threadIdx.x] = c0 + threadIdx.x < n ? diag[c0 + threadIdx.x] : 0.0;
+        const double v = c0 + threadIdx.x < n ? diag[c0 + threadIdx.x] : 0.0;
+        chunk[threadIdx.x] = sum ? v : order_key(v);
         __syncthreads();
         if (sum) {
             if (threadIdx.x == 0) {

@@ -2,6 +2,8 @@
 remainders, tile counts on both sides of the change from pairs of tiles to single ones, and the values
 for which a wave quantizes by the general form (global scales outside [2^-26, 2^26], values of 2^100 and
 beyond in some rows), zero scale codes and zero weights among them."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -59,3 +61,31 @@ def test_ldlq_huge_values_in_one_row(at):
     w[at] = 2.0 ** 101
     sc = torch.randint(1, 127, (35, 12), generator=g, device=DEV, dtype=torch.uint8)
     check_fixed(nv, w, synthetic_hessian(192, 300, 4), sc, 0.003)
+
+
+@pytest.mark.parametrize("at", [(0,), (63, 64), (0, 1, 2, 100, 191), tuple(range(192))])
+def test_ldlq_nan_on_the_diagonal(at):
+    """The order of the columns stays a permutation (the workspace's first ints; filled with other values
+    before) and the call reports a Hessian that is not positive definite."""
+    import paper_2606_07618_amd as nv
+    rows, cols = 35, 192
+    g = workloads.generator(DEV, 70, 3)
+    w = workloads.llm_weight(rows, cols, g, DEV)
+    H = synthetic_hessian(cols, 300, 5)
+    H[list(at), list(at)] = float("nan")
+    _, sc, S = nv.quantize(w, "absmax", 16)
+    nbytes = nv.nvfp4_ldlq_workspace_bytes(rows, cols)
+    ws = torch.full((nbytes,), 0x7F, dtype=torch.uint8, device=DEV)
+    q = torch.empty((rows, cols // 2), dtype=torch.uint8, device=DEV)
+    status = torch.zeros(1, dtype=torch.int32, device=DEV)
+    rc = nv.nvfp4_ldlq(w.data_ptr(), 1, rows, cols, 16, H.data_ptr(), sc.data_ptr(), S.data_ptr(), 0.01,
+                       q.data_ptr(), status.data_ptr(), ws.data_ptr(), nbytes,
+                       ctypes.c_void_p(torch.cuda.current_stream(DEV).cuda_stream))
+    torch.cuda.synchronize()
+    assert rc == 0 and int(status.item()) == 1
+    perm = ws[:4 * cols].view(torch.int32).cpu().numpy()
+    assert np.array_equal(np.sort(perm), np.arange(cols))
+    diag = torch.diagonal(H).cpu().numpy()
+    assert np.array_equal(perm, np.argsort(-np.where(np.isnan(diag), -np.inf, diag), kind="stable"))
+    with pytest.raises(nv.NVFP4Error):
+        nv.ldlq(w, H, sc, S, 16)

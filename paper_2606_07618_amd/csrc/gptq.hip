@@ -472,13 +472,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
 
 // X[inv[c]][r] = w[r][c]: the weights by columns, in the visiting order.  64 x 64 values per
 // workgroup through LDS, so that both sides move whole lines: [4096, 4096] bf16 46 us (gathered
-// row by row in the visiting order 64).
+// row by row in the visiting order 64).  One dimension of workgroups (a row block's column tiles
+// after another): the second of a grid is limited to 65535 by some runtimes, 4.2 million rows.
 template <typename In>
 __global__ __launch_bounds__(256) void init_x_kernel(const In* __restrict__ w, const int* __restrict__ inv,
                                                      int64_t rows, int64_t n, double* __restrict__ X) {
     __shared__ float v[kTile][kTile + 1];
     __shared__ int to[kTile];
-    const int64_t c0 = (int64_t)blockIdx.x * kTile, r0 = (int64_t)blockIdx.y * kTile;
+    const uint32_t tiles = (uint32_t)(n / kTile);
+    const int64_t c0 = (int64_t)(blockIdx.x % tiles) * kTile, r0 = (int64_t)(blockIdx.x / tiles) * kTile;
     const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
     for (int k = part; k < kTile; k += 4)
         if (r0 + k < rows) v[k][lane] = load_w<In>(w, (r0 + k) * n + c0 + lane);
@@ -842,8 +844,8 @@ int run_ldlq(const void* wv, int64_t rows, int64_t n, int block, const double* H
     const int64_t tiles = n / kTile;
     hipLaunchKernelGGL(init_a_kernel, dim3((unsigned)((tiles + 7) / 8 * 8 * tiles)), dim3(256), 0, st, H, perm, lambda,
                        n, Uc);
-    hipLaunchKernelGGL(init_x_kernel<In>, dim3((unsigned)(n / kTile), blocks_for(rows, kTile)), dim3(256), 0, st,
-                       w, inv, rows, n, X);
+    hipLaunchKernelGGL(init_x_kernel<In>, dim3((unsigned)(tiles * blocks_for(rows, kTile))), dim3(256), 0, st, w, inv,
+                       rows, n, X);
     // factor, from the last block: its diagonal block, then per block the panel above it, the
     // column of tiles the next diagonal block and panel need, and then the next diagonal block
     // beside the rest of the trailing update (look-ahead)

@@ -89,3 +89,19 @@ def test_ldlq_nan_on_the_diagonal(at):
     assert np.array_equal(perm, np.argsort(-np.where(np.isnan(diag), -np.inf, diag), kind="stable"))
     with pytest.raises(nv.NVFP4Error):
         nv.ldlq(w, H, sc, S, 16)
+
+
+def test_ldlq_more_row_blocks_than_a_grids_second_dimension():
+    """65537 blocks of 64 rows, the last of one row: the launch of every kernel of the pass.  Rows do not
+    depend on each other, so the first and the last ones are compared."""
+    import paper_2606_07618_amd as nv
+    rows, cols = 65536 * 64 + 1, 64
+    g = workloads.generator(DEV, 70, 4)
+    w = (torch.randn((rows, cols), generator=g, device=DEV) * 0.02).to(torch.bfloat16)
+    H = synthetic_hessian(cols, 300, 6)
+    _, sc, S = nv.quantize(w, "absmax", 16)
+    got = nv.ldlq(w, H, sc, S, 16)
+    for sel in (slice(0, 70), slice(rows - 70, rows)):
+        ref = oracle.ldlq(workloads.host_array(w[sel]), H.cpu().numpy(), sc[sel].cpu().numpy(), float(S.item()), 16, 0.01)
+        part = got[sel].cpu().numpy()
+        assert np.array_equal(part, ref), describe_mismatch(part, ref, "nibbles")

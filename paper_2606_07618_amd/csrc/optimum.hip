@@ -267,9 +267,18 @@ __global__ __launch_bounds__(Spread<N>::kThreads, 5) void optimum_kernel(const I
         __syncthreads();
         for (int b = 0; b < KB && blk0 + b < nblocks; ++b) {
             const double *ad = ads[b], *wd = wds[b], *aa = aas[b];
-            int nb = 0;                            // breakpoints: 7 for each non-zero element
+            // Breakpoints: 7 for each non-zero finite element.  An infinity or a NaN has none (its keys
+            // would not be ordered, and an element must not have more than 7 positions): the loss is
+            // infinite or NaN whatever the scale.
+            int nb = 0;
+            bool zero = true;
 #pragma unroll
-            for (int i = 0; i < N; i += kWave) nb += 7 * __popcll(__ballot(i + lane < N && ad[(i + lane) & (N - 1)] != 0.0));
+            for (int i = 0; i < N; i += kWave) {
+                const double a = ad[(i + lane) & (N - 1)];
+                const uint64_t nonzero = __ballot(i + lane < N && a != 0.0);
+                zero = zero && nonzero == 0;
+                nb += 7 * __popcll(nonzero & __ballot(a < INFINITY));
+            }
             double k[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -278,8 +287,9 @@ __global__ __launch_bounds__(Spread<N>::kThreads, 5) void optimum_kernel(const I
                 const bool up = (e & 1) == 0, pad = h == (up ? 7 : 0);
                 const double a = ad[e];
                 const double v = a * break_factor(pad ? 0 : up ? 6 - h : h - 1);
-                k[r] = pad || a == 0.0 ? INFINITY
-                                       : __longlong_as_double(__double_as_longlong(v) | (long long)e);
+                k[r] = pad || a == 0.0 || !(a < INFINITY)
+                           ? INFINITY
+                           : __longlong_as_double(__double_as_longlong(v) | (long long)e);
                 // the element's terms with h breakpoints passed: rounded to value 7 - h
                 const double g = e2m1_value(7 - h), w = wd[e];
                 tab[p] = a == 0.0 ? make_double2(0.0, 0.0) : make_double2(w * a * g, w * g * g);
@@ -375,7 +385,7 @@ __global__ __launch_bounds__(Spread<N>::kThreads, 5) void optimum_kernel(const I
                     if (better(wave_best[v], best)) best = wave_best[v];
             }
             double J = best.val, s_opt = best.s;
-            if (nb == 0) {                          // all-zero block: zero loss at any scale
+            if (zero) {                             // all-zero block: zero loss at any scale
                 J = 0.0;
                 s_opt = 1.0;
             }

@@ -37,3 +37,30 @@ def test_optimum_ties_and_partial_batches(n, count):
         got = nv.block_optimum(xt, S, n, None if weight is None else torch.from_numpy(weight).to(DEV))
         torch.cuda.synchronize()
         compare_optimum(got, oracle_blocks(workloads.host_array(xt), 1.0, n, weight), f"n {n} count {count}")
+
+
+@pytest.mark.parametrize("n", [16, 32, 64, 128])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_optimum_nonfinite_elements(n, bad):
+    """A block with an infinity or a NaN has that loss, at the all-zero reconstruction; its neighbours are
+    what they are without it.  One such element (first, middle, last), several, and a block of nothing else."""
+    import paper_2606_07618_amd as nv
+    rng = np.random.default_rng([n, 7])
+    x = rng.standard_normal((11, n)).astype(np.float32)
+    x[9] = 0.0
+    S = torch.ones(1, device=DEV)
+    clean = [t.cpu().numpy().reshape(-1) for t in nv.block_optimum(torch.from_numpy(x).to(DEV), S, n)]
+    rows = [1, 3, 4, 6, 8]
+    for r, at in zip(rows, ([0], [n // 2], [n - 1], list(range(0, n, 3)), list(range(n)))):
+        x[r, at] = bad
+    for weight in (None, torch.ones(n, device=DEV)):
+        got = [t.cpu().numpy().reshape(-1) for t in nv.block_optimum(torch.from_numpy(x).to(DEV), S, n, weight)]
+        torch.cuda.synchronize()
+        for r in range(11):
+            if r not in rows:
+                assert all(g[r] == c[r] for g, c in zip(got, clean)), r
+                continue
+            loss, scale, code, fp8 = (g[r] for g in got)
+            assert np.isnan(loss) if np.isnan(bad) else loss == np.inf
+            assert scale == np.inf and code == 126
+            assert np.isnan(fp8) if np.isnan(bad) else fp8 == np.inf

@@ -65,7 +65,7 @@ struct Spread {
     static constexpr int kThreads = kWaves * kWave;
     static constexpr int kBreaks = 8 * N;
     static constexpr int kPer = kBreaks / kThreads;            // 2 at N = 16, else 4
-    // Blocks a workgroup takes together: their elements are loaded, and their FP8 neighbours
+    // Most blocks that a workgroup takes together: their elements are loaded, and their FP8 neighbours
     // scored, by full waves.
     // (At N = 32 the extra registers cost the fifth wave per SIMD and 5 % of the time.)
     static constexpr int kBatch = N == 16 ? 4 : 1;
@@ -231,21 +231,21 @@ template <typename In, int N>
 __global__ __launch_bounds__(Spread<N>::kThreads, 5) void optimum_kernel(const In* __restrict__ x,
                                                                      const float* __restrict__ colw,
                                                                      const float* __restrict__ tensor_scale,
-                                                                     int64_t nblocks, int64_t bpr,
+                                                                     int64_t nblocks, int64_t bpr, int batch,
                                                                      double* __restrict__ opt_loss,
                                                                      double* __restrict__ opt_scale,
                                                                      uint8_t* __restrict__ fp8_code,
                                                                      double* __restrict__ fp8_loss) {
     using Sp = Spread<N>;
     constexpr int R = Sp::kPer, W = Sp::kWaves, P = Sp::kBreaks;
-    constexpr int KB = Sp::kBatch;
+    const int KB = Sp::kBatch == 1 ? 1 : batch;
     __shared__ alignas(16) double key[P];     // sorted keys, then breakpoints, then FP8 loss terms
     __shared__ alignas(16) double2 tab[P];    // tab[8 i + c]: element i's terms of B and C with c
                                               // of its breakpoints passed
-    __shared__ alignas(16) double ads[KB][N], wds[KB][N], aas[KB][N];   // |y|, w, w y^2
+    __shared__ alignas(16) double ads[Sp::kBatch][N], wds[Sp::kBatch][N], aas[Sp::kBatch][N];   // |y|, w, w y^2
     __shared__ uint32_t first[W > 1 ? W : 1][W > 1 ? N : 1];   // breakpoints below a wave's pieces
     __shared__ Best wave_best[W];
-    __shared__ double scale_of[KB];
+    __shared__ double scale_of[Sp::kBatch];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const float S = tensor_scale[0];
     const bool weighted = colw != nullptr;
@@ -508,14 +508,21 @@ int check_tensor(const void* x, int dtype, int64_t rows, int64_t cols, int block
     return NVFP4_OK;
 }
 
+// Up to this many blocks of 16 take a workgroup each instead of sharing one by fours: until the CUs have
+// had their 20 waves twice, a batch is a chain of four.  Alone and by fours, bfloat16 with weights: 256
+// blocks 6.9 / 16.4 us (binary32 unweighted 6.8 / 16.3), 4096 11.1 / 17.3, 10240 20.4 / 23.3, 16384
+// 29.2 / 28.4, 262144 361 / 316.
+constexpr int64_t kSingleBlocks = 10240;
+
 template <typename In, int N>
 hipError_t launch_optimum(const void* x, const float* colw, const float* S, int64_t nblocks,
                           int64_t bpr, double* opt_loss, double* opt_scale, uint8_t* code,
                           double* fp8_loss, hipStream_t st) {
-    const int64_t groups = (nblocks + Spread<N>::kBatch - 1) / Spread<N>::kBatch;
+    const int batch = nblocks <= kSingleBlocks ? 1 : Spread<N>::kBatch;
+    const int64_t groups = (nblocks + batch - 1) / batch;
     const int64_t grid = groups < 65536 ? groups : 65536;      // grid-stride over blocks
     hipLaunchKernelGGL((optimum_kernel<In, N>), dim3((unsigned)grid), dim3(Spread<N>::kThreads), 0, st,
-                       static_cast<const In*>(x), colw, S, nblocks, bpr, opt_loss, opt_scale,
+                       static_cast<const In*>(x), colw, S, nblocks, bpr, batch, opt_loss, opt_scale,
                        code, fp8_loss);
     return hipGetLastError();
 }

@@ -39,6 +39,12 @@ def test_optimum_ties_and_partial_batches(n, count):
         compare_optimum(got, oracle_blocks(workloads.host_array(xt), 1.0, n, weight), f"n {n} count {count}")
 
 
+# the most blocks of 16 that take a workgroup each, and more of them, four to a workgroup, with remainders
+@pytest.mark.parametrize("count", [10240, 10241, 10242, 10243, 10244])
+def test_optimum_single_blocks_and_batches(count):
+    test_optimum_ties_and_partial_batches(16, count)
+
+
 @pytest.mark.parametrize("n", [16, 32, 64, 128])
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
 def test_optimum_nonfinite_elements(n, bad):

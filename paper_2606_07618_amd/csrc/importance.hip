@@ -37,7 +37,7 @@ constexpr int kMaxGroups = 64;
 // One wavefront per (64 columns, chunk of rows).  The order of the sums is fixed: every column is
 // added row by row down its chunk, so one lane walks one column.  What bounds the pass is memory
 // (2 or 4 bytes and two binary64 instructions an element), so the loads are kept apart from the
-// walk: the wave fetches a tile of kTileRows rows x 64 columns as eight 16-byte loads per lane (a
+// walk: the wave fetches a tile of 64 (bfloat16) or 32 rows x 64 columns as eight 16-byte loads per lane (a
 // row's 64 values are 8 lanes wide in bfloat16, 16 in binary32), always one tile ahead in
 // registers, and hands it to the walk through LDS, where runs of any length cost no load latency.
 // WIDE needs rows that start on 16 bytes; otherwise each lane loads its own column's values.
@@ -151,11 +151,9 @@ __device__ __forceinline__ float load_value<uint16_t>(const uint16_t* x, int64_t
     return __uint_as_float((uint32_t)x[i] << 16);
 }
 
-// The same sums straight from memory, for long runs on a grid that fills the chip several times over: no
-// tile in LDS, so twice the waves of a CU, and a run's additions wait for no second pass through LDS.
-// K [16, 8, 4096, 128] bfloat16 41.9 us a call against 44.7 through tiles; Q-like [1048576, 128]
-// binary32 114 against 118.  With short runs or few waves the tiles are the faster form ([14336,
-// 4096], runs of one row: 26.7 against 130).
+// The same sums straight from memory, eight rows of a run at a time: no tile in LDS, so more waves of a
+// CU, and a run's additions wait for no second pass through LDS.  prefer_runs says where it is the faster
+// form.
 template <typename In>
 __global__ __launch_bounds__(kLanes) void norms_runs_kernel(const In* __restrict__ x, int64_t rows,
                                                             int64_t cols, int64_t group_rows,
@@ -201,6 +199,29 @@ __global__ __launch_bounds__(kLanes) void norms_runs_kernel(const In* __restrict
     if (c < cols)
         for (int g = 0; g < gout; ++g)
             part[((int64_t)blockIdx.y * gout + g) * cols + c] = acc_g[g][lane];
+}
+
+// Whether runs straight from memory are the faster form (waves: the grid; run: rows of a run; wide: rows
+// start on 16 bytes).  Measured on [rows, 64 to 4096], time of the tiles / of the runs:
+//  * runs shorter than its eight rows in flight leave it one load at a time: 0.14 to 0.83 (1.03 at most);
+//  * rows that do not start on 16 bytes: the tiles' narrow loads take as long as the walk.  Runs of 16 rows
+//    and more 1.6 to 1.95 up to 256 waves, 1.0 to 1.6 above; runs of 8 exactly 1.0 to 1.6; of 9 to 15,
+//    1.1 to 1.5 up to 256 waves, 0.64 to 0.94 on 1024, 0.8 to 1.4 on 4096 and more;
+//  * otherwise, with runs of 16 rows and more: binary32 (twice the tiles) on at most 320 waves 1.0 to 1.19,
+//    on 400 waves 0.8 to 0.9, of more than 32 groups 0.85;
+//  * a grid of 16 waves a CU, which keep the memory busy by themselves, or whose tiles a CU cannot hold at
+//    once: bfloat16 1.01 to 1.13, binary32 0.97 to 1.12, as long as a CU holds them in this form: with
+//    more groups it does not, 0.55 to 1.0;
+//  * any other grid: 0.6 to 1.04.
+bool prefer_runs(int64_t waves, int64_t run, int64_t gout, bool wide, bool f32) {
+    constexpr int64_t kCus = 256, kFull = 16, kMost = 32, kLdsBytes = 160 * 1024, kTileBytes = 8192;
+    if (run < 8) return false;
+    if (!wide) return run >= 16 || run == 8 || waves <= kCus || waves >= kFull * kCus;
+    if (run < 16) return false;
+    if (waves <= kCus * 5 / 4) return f32 && gout <= 32;
+    const int64_t a_cu = (waves + kCus - 1) / kCus, held = a_cu < kMost ? a_cu : kMost;
+    const int64_t acc_bytes = gout * kLanes * (int64_t)sizeof(double);
+    return (waves >= kFull * kCus || held * (kTileBytes + acc_bytes) > kLdsBytes) && held * acc_bytes <= kLdsBytes;
 }
 
 // One workgroup per (group, 64 columns): 16 waves each add a contiguous sixteenth of the chunk
@@ -286,8 +307,9 @@ int nvfp4_channel_sq_norms(const void* x, int dtype, int64_t rows, int64_t cols,
                            (int)gout, cr, part);
     };
     const bool wide = ((uintptr_t)x & 15) == 0 && cols * (dtype == NVFP4_IN_F32 ? 4 : 2) % 16 == 0;
-    // runs of at least a smallest chunk, and 16 waves for each of the 256 CUs
-    const bool runs = gout > 1 && group_div * group_rows >= kMinChunkRows && (int64_t)grid.x * grid.y >= 4096;
+    // rows of a run, 16 standing for more
+    const int64_t run = (group_div < 16 ? group_div : 16) * (group_rows < 16 ? group_rows : 16);
+    const bool runs = prefer_runs((int64_t)grid.x * grid.y, run, gout, wide, dtype == NVFP4_IN_F32);
     if (rows > 0 && runs && dtype == NVFP4_IN_F32)
         launch(norms_runs_kernel<float>, static_cast<const float*>(x));
     else if (rows > 0 && runs)

@@ -50,3 +50,37 @@ def test_norms_long_runs(rows, args):
     ref = reference(x, *args)
     # at most 2^19 additions of rounding 2^-53 each on either side, then one rounding to binary32
     assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= ref * (2.0 ** -24 + 2.0 ** -33))
+
+
+# Both forms of the pass (through tiles, and runs straight from memory) add in one order.  A bfloat16
+# matrix, its exact binary32 widening, and the same values one element off 16 bytes meet the rule between
+# them on both sides: runs of 7, 8, 9, 15 and 16 rows, 1, 256, 257, 320 and 321 workgroups of 64 columns.
+@pytest.mark.parametrize("chunks", [1, 256, 257, 320, 321])
+@pytest.mark.parametrize("args", [(7, 3, 1, 1), (8, 2, 1, 1), (3, 6, 3, 1), (15, 2, 1, 2), (16, 1, 1, 1), (100, 33, 1, 1), (2, 64, 8, 1)])
+def test_norms_forms_agree(chunks, args):
+    check_forms(256 * chunks - 3, 64, args)
+
+
+# 2, 10 and 11 workgroups a CU of 16 groups (a CU holds ten of their tiles), 6 and 7 of 32 (it holds six), 16
+# of both (it does not hold 16 of the runs of 32 groups)
+@pytest.mark.parametrize("chunks,cols,groups", [(256, 128, 16), (1280, 128, 16), (1281, 128, 16), (768, 128, 32), (769, 128, 32), (2048, 128, 16),
+                                                (2047, 128, 32), (2048, 128, 32), (2048, 65, 32)])
+@pytest.mark.parametrize("run", [9, 40])
+def test_norms_forms_agree_on_large_grids(chunks, cols, groups, run):
+    check_forms(256 * chunks, cols, (run, groups, 1, 1))
+
+
+def check_forms(rows, cols, args):
+    import paper_2606_07618_amd as nv
+    g = workloads.generator(DEV, 93, rows, cols)
+    x = torch.randn((rows, cols), generator=g, device=DEV).to(torch.bfloat16)
+    got = nv.channel_sq_norms(x, *args)
+    ref = reference(x, *args)
+    # a group's additions, at most one a row, of rounding 2^-53 each, then one rounding to binary32 (2^-24)
+    assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - ref) <= ref * (2.0 ** -24 + rows * 2.0 ** -53))
+    for dtype in (torch.bfloat16, torch.float32):
+        buf = torch.empty(x.numel() + 1, dtype=dtype, device=DEV)
+        buf[1:].copy_(x.reshape(-1))
+        for other in (x.to(dtype), buf[1:].view(rows, cols)):
+            again = nv.channel_sq_norms(other, *args)
+            assert torch.equal(got.view(torch.int32), again.view(torch.int32))

@@ -1,5 +1,5 @@
-"""The SwiGLU producer's two forms on the GPU: lanes whose 16 gates all lie inside (-80, 80) and lanes
-with one that does not, at the limit and beyond, and every gate inside with several factors; bit for
+"""The SwiGLU producer's two forms on the GPU: waves whose gates (16 a lane) all lie inside (-80, 80) and
+waves with one that does not, at the limit and beyond, and every gate inside with several factors; bit for
 bit against the oracle."""
 import numpy as np
 import pytest
@@ -39,3 +39,15 @@ def test_every_gate_in_range(seed):
     gate = np.concatenate([bits, bits | 0x8000]).reshape(-1, 32)
     up = (np.random.default_rng(seed).standard_normal(gate.shape).astype(np.float32).view(np.uint32) >> 16)
     check(nv, gate, up.astype(np.uint16))
+
+
+@pytest.mark.parametrize("wave", [0, 1, 4, 6])
+@pytest.mark.parametrize("lane_at", [0, 63])
+def test_one_wave_out_of_range(wave, lane_at):
+    """Seven waves of 1024 gates (the last one short), one of them with a gate at the limit."""
+    import paper_2606_07618_amd as nv
+    rng = np.random.default_rng([wave, lane_at])
+    gate = (rng.standard_normal(6 * 1024 + 1008).astype(np.float32) * 3).view(np.uint32) >> 16
+    up = rng.standard_normal(gate.size).astype(np.float32).view(np.uint32) >> 16
+    gate[min(wave * 1024 + lane_at * 16 + 5, gate.size - 1)] = 0x42A0
+    check(nv, gate.astype(np.uint16).reshape(-1, 48), up.astype(np.uint16).reshape(-1, 48))

@@ -103,9 +103,13 @@ NOALLOC_MAX_TENSORS = 32
 METHOD_IDS = {"absmax": 0, "four_over_six": 1, "scalesweep_mse": 2, "scalesweep_wmse": 3}
 
 
-# The functions' argument types convert plain numbers, and the raw handle of the current stream
-# needs no stream object: a call on a small tensor is as long as its host path (one activation row
-# [1, 4096]: 10.7 -> 9.3 us a call).
+# The functions' argument types convert the wrapper's own numbers, and the raw handle of the current
+# stream needs no stream object: a call on a small tensor is as long as its host path (one activation row
+# [1, 4096]: 10.7 -> 9.3 us a call).  A caller's real numbers are converted first, so that what is no
+# number raises what that conversion raises (TypeError, OverflowError), not ctypes.ArgumentError.
+_float, _double = ctypes.c_float, ctypes.c_double
+
+
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -156,7 +160,7 @@ def quantize(x: torch.Tensor, method: str = "scalesweep_wmse", block: int = 16,
         ws = workspace(x.device)
     wsb = 0 if ws is None else ws.numel() * ws.element_size()
     common = (_ptr(x), dt, rows, cols, block)
-    tail = (D, static_scale, _ptr(S), _ptr(q), _ptr(sc), _ptr(ws), wsb, _stream(x))
+    tail = (D, _float(static_scale), _ptr(S), _ptr(q), _ptr(sc), _ptr(ws), wsb, _stream(x))
     if weight is not None:
         if not (weight.is_cuda and weight.dtype == torch.float32 and weight.is_contiguous()
                 and weight.numel() == cols):
@@ -216,7 +220,7 @@ def quantize_window(x: torch.Tensor, block: int = 16, weight: torch.Tensor | Non
         raise ValueError("weight must be a contiguous float32 device tensor of length cols")
     rc = nvfp4_quant_scalesweep_window(
         _ptr(x), dt, rows, cols, block, _ptr(weight), WINDOW_MODES[mode], int(lo), int(hi),
-        fp8_range, static_scale, _ptr(S), _ptr(q), _ptr(sc), _ptr(ws), wsb, _stream(x))
+        _float(fp8_range), _float(static_scale), _ptr(S), _ptr(q), _ptr(sc), _ptr(ws), wsb, _stream(x))
     if rc != 0:
         raise NVFP4Error(rc, "nvfp4_quant_scalesweep_window")
     return q, sc, S
@@ -385,8 +389,8 @@ def quantize_online(x: torch.Tensor, method: str, static_scale: float, block: in
     else:
         q, sc = out
     rc = nvfp4_quant_online(METHOD_IDS[method], _ptr(x), dt, rows, cols, block, _ptr(importance),
-                            imp_groups, imp_group_rows, static_scale, lay, None, _ptr(q), _ptr(sc),
-                            _stream(x))
+                            imp_groups, imp_group_rows, _float(static_scale), lay, None, _ptr(q),
+                            _ptr(sc), _stream(x))
     if rc != 0:
         raise NVFP4Error(rc, "nvfp4_quant_online")
     if layout == "row_major" and out is None:
@@ -434,8 +438,8 @@ def quantize_online_swiglu(gate: torch.Tensor, up: torch.Tensor, method: str, st
     else:
         q, sc = out
     rc = nvfp4_quant_online_swiglu(METHOD_IDS[method], _ptr(gate), _ptr(up), rows, cols,
-                                   _ptr(importance), imp_groups, imp_group_rows, static_scale, lay,
-                                   None, _ptr(q), _ptr(sc), _stream(gate))
+                                   _ptr(importance), imp_groups, imp_group_rows, _float(static_scale),
+                                   lay, None, _ptr(q), _ptr(sc), _stream(gate))
     if rc != 0:
         raise NVFP4Error(rc, "nvfp4_quant_online_swiglu")
     if layout == "row_major" and out is None:
@@ -482,7 +486,7 @@ def ldlq(w: torch.Tensor, hessian: torch.Tensor, scales: torch.Tensor, S: torch.
     q = torch.empty((rows, cols // 2), dtype=torch.uint8, device=w.device)
     status = torch.empty(1, dtype=torch.int32, device=w.device)
     rc = nvfp4_ldlq(_ptr(w), dt, rows, cols, block, _ptr(hessian), _ptr(scales), _ptr(S),
-                    damp, _ptr(q), _ptr(status), _ptr(ws), nbytes, _stream(w))
+                    _double(damp), _ptr(q), _ptr(status), _ptr(ws), nbytes, _stream(w))
     if rc != 0:
         raise NVFP4Error(rc, "nvfp4_ldlq")
     if check and int(status.item()) != 0:

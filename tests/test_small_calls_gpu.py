@@ -1,6 +1,6 @@
-"""Small calls on the GPU: the padding of swizzled scales at the edges of its 128 x 4 tiles, written by
-the launch that quantizes, and the dynamic global scale on both sides of the grid size up to which
-every workgroup folds the reduction's partial maxima itself."""
+"""Small calls on the GPU: what is no real number refused as Python does; the padding of swizzled scales at
+the edges of its 128 x 4 tiles, written by the launch that quantizes; and the dynamic global scale on both
+sides of the grid size up to which every workgroup folds the reduction's partial maxima itself."""
 import numpy as np
 import pytest
 import torch
@@ -76,3 +76,19 @@ def test_four_elements_a_lane(rows, cols, method, dtype):
     assert S.item() == S_ref
     assert np.array_equal(sc.cpu().numpy(), sc_ref)
     assert np.array_equal(q.cpu().numpy(), q_ref)
+
+
+@pytest.mark.parametrize("bad,error", [("0.5", TypeError), (None, TypeError), ([0.5], TypeError), (10 ** 400, OverflowError)])
+def test_what_is_no_real_number(bad, error):
+    import paper_2606_07618_amd as nv
+    x = torch.ones((64, 64), dtype=torch.bfloat16, device=DEV)
+    H = torch.eye(64, dtype=torch.float64, device=DEV)
+    _, sc, S = nv.quantize(x, "absmax", 16)
+    for call in (lambda: nv.quantize(x, "absmax", 16, static_scale=bad),
+                 lambda: nv.quantize_window(x, 16, static_scale=bad),
+                 lambda: nv.quantize_window(x, 16, fp8_range=bad),
+                 lambda: nv.quantize_online(x, "absmax", bad),
+                 lambda: nv.quantize_online_swiglu(x, x, "absmax", bad),
+                 lambda: nv.ldlq(x, H, sc, S, 16, damp=bad)):
+        with pytest.raises(error):
+            call()

@@ -110,6 +110,13 @@ METHOD_IDS = {"absmax": 0, "four_over_six": 1, "scalesweep_mse": 2, "scalesweep_
 _float, _double = ctypes.c_float, ctypes.c_double
 
 
+try:
+    from torch._C import _cuda_getCurrentRawStream as _raw_stream
+except ImportError:                                  # not part of torch's public interface
+    def _raw_stream(index):
+        return torch.cuda.current_stream(index).cuda_stream
+
+
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -119,7 +126,7 @@ def _stream(t):
     index = t.get_device()
     if index < 0:                                    # it would stand for the current device
         raise ValueError(f"Expected a cuda device, but got: {t.device}")
-    return torch._C._cuda_getCurrentRawStream(index)
+    return _raw_stream(index)
 
 
 def workspace(device) -> torch.Tensor:

@@ -284,3 +284,16 @@ def test_swiglu_validation(nv):
     assert p(FAKE, None, 4, 64, FAKE, None) == -1
     assert p(FAKE, FAKE, 4, 64, P(0x100004), None) == -7
     assert p(FAKE, FAKE, 0, 64, FAKE, None) == 0
+
+
+def test_binding_without_torchs_raw_stream_call():
+    """The binding takes a stream's raw handle from torch.cuda.current_stream where torch has no call for it."""
+    import subprocess
+    import sys
+    code = ("import torch\n"
+            "del torch._C._cuda_getCurrentRawStream\n"
+            "from types import SimpleNamespace as N\n"
+            "torch.cuda.current_stream = lambda index: N(cuda_stream=1000 + index)\n"
+            "import paper_2606_07618_amd.nvfp4 as m\n"
+            "assert m._stream(N(get_device=lambda: 3)) == 1003\n")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT)

@@ -178,8 +178,8 @@ int64_t nvfp4_scales_bytes(int64_t rows, int64_t cols, int block, int layout);
  *   ((m / 128) * kt + k / 4) * 512 + (m mod 32) * 16 + ((m / 32) mod 4) * 4 + k mod 4
  * for row m, scale column k, kt = ceil(cols / 64) -- and zeroes its padding; the buffer holds
  * nvfp4_scales_bytes() bytes.  tensor_scale: NULL, or a device float that receives S.  No
- * workspace, no reduction pass: one quantization kernel (plus a padding kernel for the
- * swizzled layout), asynchronous on `stream`.  Other errors as the single-tensor calls. */
+ * workspace, no reduction pass: one quantization kernel, which writes the swizzled layout's
+ * padding too, asynchronous on `stream`.  Other errors as the single-tensor calls. */
 int nvfp4_quant_online(int method, const void* x, int dtype, int64_t rows, int64_t cols, int block,
                        const float* importance, int64_t imp_groups, int64_t imp_group_rows,
                        float static_scale, int scale_layout, float* tensor_scale, uint8_t* q,
@@ -319,8 +319,8 @@ int nvfp4_dequant(const uint8_t* q, const uint8_t* scales, const float* tensor_s
  * FP8-quantized optimal scale (appendix, second paragraph): of the two E4M3 values just below
  * and just above opt_scale[b] (codes >= 1), the one with the lower L, the lower one on a tie:
  * fp8_code[b] its code and fp8_loss[b] its loss.  opt_loss [nblocks] is required (8-byte
- * aligned); opt_scale, fp8_code and fp8_loss may be NULL.  One wavefront per block; binary64
- * ALU-bound. */
+ * aligned); opt_scale, fp8_code and fp8_loss may be NULL.  One wavefront per block (two at block 64,
+ * four at 128); bound by vector instruction issue. */
 int nvfp4_block_optimum(const void* x, int dtype, int64_t rows, int64_t cols, int block,
                         const float* col_weight, const float* tensor_scale, double* opt_loss,
                         double* opt_scale, uint8_t* fp8_code, double* fp8_loss, void* stream);

@@ -143,10 +143,12 @@ __global__ __launch_bounds__(64 * kOrderParts) void order_kernel(const double* _
 }
 
 // ---- factor: blocked, from the last 64-column block backwards ---------------------------
-// Uc holds A = Hp column-major (Uc[j n + i] = A_ij for i <= j; the lower triangle is never
-// written, and the values the kernels read from it feed only results they discard) and is
-// overwritten in place by U.  Element (i, j) must receive its terms k = n-1, n-2, ..., j+1 in that order; the blocks
-// are finished last-first and every kernel walks k downwards, so it does.
+// Uc holds A = Hp column-major (Uc[j n + i] = A_ij for i <= j) and is overwritten in place by U.
+// Below the diagonal blocks it receives U by rows as well (Uc[i n + j] = U_ij for j > i in a later
+// block: factor_panel_kernel writes it, the quantization reads it); inside them the lower triangle
+// is never written, and the values read from it feed only results that are discarded.  Element
+// (i, j) must receive its terms k = n-1, n-2, ..., j+1 in that order; the blocks are finished
+// last-first and every kernel walks k downwards, so it does.
 
 // The damped, reordered Hessian, its upper triangle only (only that is read as A), 64 x 64 values per
 // workgroup through LDS: read along the rows of H (64 values scattered over one row of 8 n bytes),

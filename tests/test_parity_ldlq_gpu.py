@@ -64,9 +64,9 @@ def test_ldlq_parity_many_tiles_every_row(nv, rows, cols):
 
 def test_ldlq_workspace_contents_do_not_matter(nv):
     """The C call on a caller workspace filled with NaN, then reused for a second problem: only
-    the upper triangle of the permuted Hessian is written and read as A, and whatever the
-    kernels read elsewhere in the workspace feeds only discarded values, so both calls match
-    the oracle."""
+    the upper triangle of the permuted Hessian is written and read as A, the lower one is read
+    only where the panel has written U by rows, and whatever the kernels read elsewhere in the
+    workspace feeds only discarded values, so both calls match the oracle."""
     import ctypes
     rows, cols, block = 40, 256, 16
     nbytes = nv.nvfp4_ldlq_workspace_bytes(rows, cols)

@@ -38,7 +38,7 @@ VALU_PEAK_TOPS = 256 * 4 * 32 * 2.4e9 / 1e12    # 78.64 T lane-ops/s (an FMA is 
 OPS_PER_EVAL = {"scalesweep_mse": 4, "scalesweep_wmse": 5}
 CANDIDATES_16 = {"scalesweep_mse": 11, "scalesweep_wmse": 16}
 DOMINANT = "scalesweep_wmse"
-DOMINANT_SYMBOL = "quant_kernel<3, unsigned short, 16, false>"
+DOMINANT_SYMBOL = "quant_kernel<3, unsigned short, 16, false, false, 16>"
 
 
 def parse():

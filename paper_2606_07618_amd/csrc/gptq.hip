@@ -92,7 +92,7 @@ __global__ __launch_bounds__(256) void diag_kernel(const double* __restrict__ H,
 // counts over a sixteenth of every 1024-value chunk of the diagonal staged in LDS (one value per
 // step, read by the wave's lanes alike), and the sixteen counts are added.
 // Beside them, the last workgroup: lambda = damp * (sum of the diagonal in index order) / n, one lane
-// adding the staged chunks.  At n = 4096 the sum is 31 us of dependent additions, the order 24 us.
+// adding the staged chunks.  At n = 4096 the two take 25 us side by side.
 constexpr int kOrderParts = 16;
 __global__ __launch_bounds__(64 * kOrderParts) void order_kernel(const double* __restrict__ diag, int64_t n,
                                                                  int* __restrict__ perm, int* __restrict__ inv,
@@ -815,8 +815,10 @@ Layout layout_of(int64_t rows, int64_t n) {
 }
 
 // The last tiles, whose terms go tile by tile: their launches are as long as a tile's own chain, and 64
-// terms are half the work of a wave beside it.  4, 16 and 28 of them: 3.94, 3.82, 3.87 ms for the
-// launches of [4096, 4096].
+// terms are half the work of a wave beside it.  8, 16 and 32 of them, whole calls: [4096, 4096] 7.51, 7.50,
+// 7.48 ms, [4096, 2048] 2.60, 2.59, 2.59, [4096, 8192] 30.2, 30.1, 30.0, [14336, 4096] 16.94, 16.96, 17.27,
+// [14336, 2048] 5.10, 5.08, 5.28.  With few rows the chain is the longer role for longer, and more would be
+// the better: [128, 4096] 4.93, 4.87, 4.72.
 constexpr int64_t kSingleTiles = 16;
 
 unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }

@@ -327,7 +327,7 @@ __device__ __forceinline__ float silu_in_range(float g) {
 }
 
 // The 16 producer outputs of one lane (bfloat16 values widened to binary32, exactly).  Bound by
-// vector instructions: about 25 an element where every gate of the wave is in range, against 37 in
+// vector instructions: 26 an element where every gate of the wave is in range, against 36 in
 // the general form (a range test, a division and a rounding by integers for each element).  A wave
 // takes one form: by lanes, gates out of range in some of them cost both (fused AbsMax on [4096, 64],
 // an eighth of the gates out of range, 5.38 us by lanes, 4.59 by waves; all in range 3.7 either way).
@@ -1163,7 +1163,7 @@ __global__ __launch_bounds__(kThreads) void quant_kernel(const In* __restrict__ 
     const uint32_t tile = SWZ ? xcd_tile(blockIdx.x, p.tiles) : blockIdx.x;
     // The arguments behind the weights' address are fetched with those behind the tile's: left to the
     // compiler they wait for a second round of scalar loads, ahead of the weights' own (a layer, WMSE:
-    // 464.9 us against 461.5).
+    // 470.7 us against 467.2, the time it took with fewer arguments; binary32 553.9 against 547.8).
     if constexpr (WEIGHTED_OBJ)
         asm volatile("" ::"s"(colw), "s"(p.bpr_magic), "s"(p.wgroups), "s"(p.wgr_magic), "s"(p.wgn_magic));
     const int lane = threadIdx.x & 63;
@@ -1585,7 +1585,9 @@ int64_t quant_grid(const Call& c) {
 // elements are the call's length until the SIMDs hold several waves.  Measured, 16 against 4 a lane
 // (bfloat16, swizzled scales): MSE on [1, 4096] 4.95 / 3.54 us, 64 workgroups 6.89 / 5.68, 256 of them
 // 7.39 / 6.92 (binary32 7.71 / 8.44), 512 8.12 / 9.08; AbsMax 2.93 / 2.63, 3.09 / 2.69, 3.22 / 3.10,
-// 3.44 / 3.82; four-over-six on 64 4.60 / 4.48, on 256 4.71 / 4.87.
+// 3.44 / 3.82; four-over-six on 64 4.60 / 4.48, on 256 4.71 / 4.87.  On 128 every method and type gains
+// (row-major): MSE 6.79 / 5.80 (binary32 6.86 / 6.37), AbsMax 2.84 / 2.42 (2.99 / 2.44), four-over-six
+// 4.80 / 4.39 (4.95 / 4.43).
 constexpr int64_t kNarrowTiles = 128;
 
 bool narrow_lanes(const Call& c, bool next_tensor) {

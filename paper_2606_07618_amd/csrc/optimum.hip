@@ -222,7 +222,7 @@ __device__ __forceinline__ double read_lane(double v, int lane) {
 // minus as many midpoints as it has breakpoints among those: a count of its positions below seg
 // (a compare, and a bit count below the lane), instead of comparisons with seven products per
 // element and piece, and the terms it adds to B and C come from a table of its eight roundings,
-// formed once.  VALU issue bounds the kernel (781 instructions a block at N = 16, of
+// formed once.  VALU issue bounds the kernel (784 instructions a block at N = 16, of
 // which the sort and the pieces take 300 each): [4096, 4096] bfloat16 with weights 1.20 ms (a
 // comparison with each product, breakpoints sorted in LDS, the FP8 losses on one lane: 4.19 ms);
 // at N = 32, 64, 128 0.83, 0.71 and 0.61 ms for half, a quarter and an eighth of the rows (2.92,

@@ -240,7 +240,7 @@ int nvfp4_channel_sq_norms(const void* x, int dtype, int64_t rows, int64_t cols,
  * them.  w: [rows, cols] binary32 or bfloat16.  cols must be a multiple of 64.  *status
  * (device int) is set to 0, or 1 if the damped Hessian is not positive definite (then q is
  * unspecified): check it after synchronizing.  workspace: >= nvfp4_ldlq_workspace_bytes()
- * bytes (about 8 cols^2 + 9 rows cols bytes), 256-byte aligned, no initialization.  All
+ * bytes (about 8 (cols^2 + 2 rows cols) bytes), 256-byte aligned, no initialization.  All
  * arithmetic is binary64 in a fixed order (no atomics), so results are deterministic. */
 size_t nvfp4_ldlq_workspace_bytes(int64_t rows, int64_t cols);
 int nvfp4_ldlq(const void* w, int dtype, int64_t rows, int64_t cols, int block, const double* hessian,

@@ -809,7 +809,8 @@ Layout layout_of(int64_t rows, int64_t n) {
     l.D = o;      o = align256(o + (size_t)n * sizeof(double));
     l.Uc = o;     o = align256(o + (size_t)n * n * sizeof(double));
     l.X = o;      o = align256(o + (size_t)rows * n * sizeof(double));
-    // unused room of 128 values a row: the size that callers reserve stays what it has been
+    // unused room of 128 values a row: the size stays what callers have been told, at 64 columns no less
+    // than the interface's 8 (cols^2 + 2 rows cols) bytes
     o = align256(o + (size_t)2 * rows * kTile * sizeof(double));
     l.codes = o;  o = align256(o + (size_t)rows * n);
     l.total = o;

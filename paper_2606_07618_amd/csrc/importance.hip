@@ -202,26 +202,25 @@ __global__ __launch_bounds__(kLanes) void norms_runs_kernel(const In* __restrict
 }
 
 // Whether runs straight from memory are the faster form (waves: the grid; run: rows of a run; wide: rows
-// start on 16 bytes).  Measured on [rows, 64 to 4096], time of the tiles / of the runs:
-//  * runs shorter than its eight rows in flight leave it one load at a time: 0.14 to 0.83 (1.03 at most);
-//  * rows that do not start on 16 bytes: the tiles' narrow loads take as long as the walk.  Runs of 16 rows
-//    and more 1.6 to 1.95 up to 256 waves, 1.0 to 1.6 above; runs of 8 exactly 1.0 to 1.6; of 9 to 15,
-//    1.1 to 1.5 up to 256 waves, 0.64 to 0.94 on 1024, 0.8 to 1.4 on 4096 and more;
-//  * otherwise, with runs of 16 rows and more: binary32 (twice the tiles) on at most 320 waves 1.0 to 1.19,
-//    on 400 waves 0.8 to 0.9, of more than 32 groups 0.85;
-//  * a grid of 16 waves a CU, which keep the memory busy by themselves, or whose tiles a CU cannot hold at
-//    once: bfloat16 1.01 to 1.13, binary32 0.97 to 1.12, as long as a CU holds them in this form: with
-//    more groups it does not, 0.55 to 1.0;
-//  * any other grid: 0.6 to 1.04.
-bool prefer_runs(int64_t waves, int64_t run, int64_t gout, bool wide, bool f32) {
-    constexpr int64_t kCus = 256, kFull = 16, kMost = 32, kLdsBytes = 160 * 1024, kTileBytes = 8192;
-    if (run < 8) return false;
-    if (!wide) return run >= 16 || run == 8 || waves <= kCus || waves >= kFull * kCus;
-    if (run < 16) return false;
-    if (waves <= kCus * 5 / 4) return f32 && gout <= 32;
-    const int64_t a_cu = (waves + kCus - 1) / kCus, held = a_cu < kMost ? a_cu : kMost;
-    const int64_t acc_bytes = gout * kLanes * (int64_t)sizeof(double);
-    return (waves >= kFull * kCus || held * (kTileBytes + acc_bytes) > kLdsBytes) && held * acc_bytes <= kLdsBytes;
+// start on 16 bytes).  A run takes its rows eight loads at a time and the rest singly, so what it waits for
+// is run / 8 + run % 8 latencies; up to a fifth of its rows (8, 16, 17, 25, 33, 40, ...) is few.  So the
+// answer also turns on where the input lies: figures are the tiles' time over the runs', cold (inputs that
+// no cache holds) and warm (one that the L2s or the memory-side cache hold).
+//  * runs of less than eight rows or many loads: 0.36 to 1.0 cold, 0.38 to 1.04 warm;
+//  * rows that do not start on 16 bytes, few loads: the tiles' narrow loads take as long as the walk.  16
+//    waves 0.96 to 1.3 cold, 1.5 to 1.95 warm; 4096 and more 1.03 to 1.5 and 1.0 to 1.6 (a quarter of the
+//    rows, runs of 9, 1.09 to 1.19 and 0.94 to 1.4); a grid whose tiles a CU cannot hold at once 1.2 to
+//    1.46; between them 0.74 to 1.0 cold, 1.0 to 1.9 warm, which stays with the tiles;
+//  * otherwise 0.37 to 0.98 cold up to 2048 waves, 0.6 to 1.2 warm; 16 waves a CU, which keep the memory
+//    busy by themselves, 0.87 to 1.09 and 0.87 to 1.13, of it runs of a smallest chunk and more.
+bool prefer_runs(int64_t waves, int64_t run, int64_t gout, bool wide) {
+    constexpr int64_t kCus = 256;
+    const bool full = waves >= 16 * kCus;
+    if (wide) return gout > 1 && run >= kMinChunkRows && full;
+    const int64_t loads = run / 8 + run % 8;
+    if (run < 8 || (full ? 4 : 5) * loads > run) return false;
+    const int64_t tile_bytes = (waves + kCus - 1) / kCus * (8192 + gout * kLanes * (int64_t)sizeof(double));   // a CU's
+    return waves <= 64 || full || tile_bytes > 160 * 1024;
 }
 
 // One workgroup per (group, 64 columns): 16 waves each add a contiguous sixteenth of the chunk
@@ -307,9 +306,10 @@ int nvfp4_channel_sq_norms(const void* x, int dtype, int64_t rows, int64_t cols,
                            (int)gout, cr, part);
     };
     const bool wide = ((uintptr_t)x & 15) == 0 && cols * (dtype == NVFP4_IN_F32 ? 4 : 2) % 16 == 0;
-    // rows of a run, 16 standing for more
-    const int64_t run = (group_div < 16 ? group_div : 16) * (group_rows < 16 ? group_rows : 16);
-    const bool runs = prefer_runs((int64_t)grid.x * grid.y, run, gout, wide, dtype == NVFP4_IN_F32);
+    // rows of a run (kMinChunkRows and more: some large number)
+    const int64_t run = (group_div < kMinChunkRows ? group_div : kMinChunkRows) *
+                        (group_rows < kMinChunkRows ? group_rows : kMinChunkRows);
+    const bool runs = prefer_runs((int64_t)grid.x * grid.y, run, gout, wide);
     if (rows > 0 && runs && dtype == NVFP4_IN_F32)
         launch(norms_runs_kernel<float>, static_cast<const float*>(x));
     else if (rows > 0 && runs)

@@ -54,19 +54,19 @@ def test_norms_long_runs(rows, args):
 
 # Both forms of the pass (through tiles, and runs straight from memory) add in one order.  A bfloat16
 # matrix, its exact binary32 widening, and the same values one element off 16 bytes meet the rule between
-# them on both sides: runs of 7, 8, 9, 15 and 16 rows, 1, 256, 257, 320 and 321 workgroups of 64 columns.
-@pytest.mark.parametrize("chunks", [1, 256, 257, 320, 321])
-@pytest.mark.parametrize("args", [(7, 3, 1, 1), (8, 2, 1, 1), (3, 6, 3, 1), (15, 2, 1, 2), (16, 1, 1, 1), (100, 33, 1, 1), (2, 64, 8, 1)])
+# them on both sides: runs of 7, 8, 9, 15, 16, 39 (rows that load singly) and 40 rows, 1 to 257 workgroups
+# of 64 columns (the shifted ones go through tiles from 65 on).
+@pytest.mark.parametrize("chunks", [1, 63, 64, 65, 257])
+@pytest.mark.parametrize("args", [(7, 3, 1, 1), (8, 2, 1, 1), (3, 6, 3, 1), (15, 2, 1, 2), (16, 1, 1, 1), (39, 2, 1, 1), (20, 4, 2, 1), (100, 33, 1, 1), (2, 64, 8, 1)])
 def test_norms_forms_agree(chunks, args):
     check_forms(256 * chunks - 3, 64, args)
 
 
-# 2, 10 and 11 workgroups a CU of 16 groups (a CU holds ten of their tiles), 6 and 7 of 32 (it holds six), 16
-# of both (it does not hold 16 of the runs of 32 groups)
-@pytest.mark.parametrize("chunks,cols,groups", [(256, 128, 16), (1280, 128, 16), (1281, 128, 16), (768, 128, 32), (769, 128, 32), (2048, 128, 16),
-                                                (2047, 128, 32), (2048, 128, 32), (2048, 65, 32)])
-@pytest.mark.parametrize("run", [9, 40])
-def test_norms_forms_agree_on_large_grids(chunks, cols, groups, run):
+# 4094 and 4096 workgroups: straight from memory at 4096, shifted rows with runs of 9 rows and more, the others
+# of 256 and more; 6 and 7 a CU of 32 groups, of which a CU holds six through tiles (shifted rows)
+@pytest.mark.parametrize("chunks,cols", [(768, 128), (769, 128), (2047, 128), (2048, 128)])
+@pytest.mark.parametrize("run,groups", [(9, 16), (40, 32), (255, 3), (256, 3), (256, 1)])
+def test_norms_forms_agree_on_large_grids(chunks, cols, run, groups):
     check_forms(256 * chunks, cols, (run, groups, 1, 1))
 
 
